@@ -233,7 +233,9 @@ double gsn_pass_bytes_per_point(gsn_grid grid, int i);
    loading its next tile after the stores, bitwise equal to e8); variant 4
    "s8" uses 8 points per thread with the
    smallest tiles that fill a wavefront, for grids too small to give every
-   compute unit a tile.  A variant changes the Stockham radix plan, the
+   compute unit a tile; variant 5 "s4" shortens the chain of latencies of a
+   pass for such grids (4 points per thread up to 256-point lines, FP64
+   exchanges, both rows of a pair together).  A variant changes the Stockham radix plan, the
    tile shape and the LDS footprint, never the result beyond rounding.
    gsn_autotune times every variant of every pass of this grid (iters launches
    each, on a scratch copy of psi: the state is not modified) and keeps the

@@ -69,13 +69,15 @@ template <int N, int V> static NKernels make_kernels()
             k.lmp_threads = LL * (N / 16);
         }
     }
+    if constexpr (V == kSmallVariant) small_kernels<N, float2>(k);
     return k;
 }
 
 template <int N> static const NKernels *variant_table(int v)
 {
     static const NKernels k[kNumVariants] = {make_kernels<N, 0>(), make_kernels<N, 1>(), make_kernels<N, 2>(),
-                                             make_kernels<N, 3>(), make_kernels<N, 4>()};
+                                             make_kernels<N, 3>(), make_kernels<N, 4>(),
+                                             make_kernels<N, kSmallVariant>()};
     return &k[v];
 }
 
@@ -203,7 +205,7 @@ static Layout compute_layout(int ndim, const int32_t n[], size_t esz = 8)
     int lmb = 0;
     for (int v = 0; v < kNumVariants; ++v) {
         const NKernels *kx = kernels_for(Nx, v), *kl = kernels_for(ndim == 3 ? Nz : Ny, v);
-        const int db = (int)((rows / 2 + kx->em_lines - 1) / kx->em_lines);
+        const int db = (int)((rows / 2 + kx->em_lines - 1) / kx->em_lines) * kx->em_parts;
         if (db > L.density_blocks) L.density_blocks = db;
         const int eb = (int)((rows + kx->em_lines - 1) / kx->em_lines);
         if (eb > L.em_blocks) L.em_blocks = eb;
@@ -336,6 +338,7 @@ static Launch lm_launch(void (*fn)(LmArgs), const NKernels *k, const LmArgs &a, 
         const int pb = persistent_blocks((const void *)fn, threads);
         if (pb > 0 && pb < grid) grid = pb;
     }
+    if (k->mass_block && a.reduce) ++grid;
     L.fn = (const void *)fn;
     L.grid = dim3(grid);
     L.block = dim3(threads);
@@ -432,7 +435,9 @@ static void build_core(gsn_grid g)
     const long long rows = g->P / Nx;
     const int H = Nx / 2;
     auto KX = [&](int pass) { return kfor(g, Nx, g->var[pass]); };
-    g->density_blocks = (int)((rows / 2 + KX(P_DENSITY)->em_lines - 1) / KX(P_DENSITY)->em_lines);
+    // mass partials of the density pass (with the Bohm term: one per block)
+    g->density_blocks = (int)((rows / 2 + KX(P_DENSITY)->em_lines - 1) / KX(P_DENSITY)->em_lines) *
+                        (g->bohm_on ? 1 : KX(P_DENSITY)->em_parts);
     auto KY = [&](int pass) { return kfor(g, Ny, g->var[pass]); };
     auto KZ = [&](int pass) { return kfor(g, Nz, g->var[pass]); };
     g->entry.clear(); g->kin_half.clear(); g->kin_full.clear(); g->nonlin.clear();
@@ -1454,6 +1459,11 @@ extern "C" gsn_status gsn_profile_passes(gsn_grid g, int64_t nsteps, double *ms,
 }
 
 // ------------------------------------------------------------------ schedule autotuning
+static_assert(kSmallVariant == kNumVariants - 1, "the autotuner leaves s4 out as the last variant");
+// Largest grid that the autotuner tries s4 on: at 2^20 points it still wins
+// the x passes of some shapes, at 2^22 none (twice the LDS per point).
+constexpr long long kSmallPoints = 1LL << 21;
+
 extern "C" int gsn_variant_count(void) { return kNumVariants; }
 
 extern "C" const char *gsn_variant_name(int v)
@@ -1611,23 +1621,27 @@ extern "C" gsn_status gsn_autotune(gsn_grid g, int iters)
     std::map<std::string, int> cache;
     if (cpath && *cpath) cache = read_cache(cpath);
     std::vector<std::string> fresh;
+    // the latency form is no candidate for grids that fill the chip
+    const int nvar = g->P > kSmallPoints ? kSmallVariant : kNumVariants;
+    bool present[P_COUNT] = {};   // passes this grid's step has
+    int from_file = 0;
     g->store_psi = 0;
     for (int p = 0; p < P_COUNT; ++p) {
         const std::string key = cache_key(g, p);
         auto it = cache.find(key);
         if (it != cache.end()) {
             g->var[p] = it->second;
+            ++from_file;
             continue;
         }
         int best = g->var[p];
         double best_ms = 1e300;
-        bool present = false;
-        for (int v = 0; v < kNumVariants; ++v) {
+        for (int v = 0; v < nvar; ++v) {
             g->var[p] = v;
             build_schedule(g);
             Launch L;
             if (!timing_launch(g, p, &L)) break;
-            present = true;
+            present[p] = true;
             // every variant starts from the same data
             if (g->have_psi)
                 HIP_TRY(hipMemcpyAsync(g->scratch, g->psi, g->esz * g->P, hipMemcpyDeviceToDevice, g->stream));
@@ -1637,7 +1651,7 @@ extern "C" gsn_status gsn_autotune(gsn_grid g, int iters)
             if (ms < best_ms) { best_ms = ms; best = v; }
         }
         g->var[p] = best;
-        if (present) fresh.push_back(key + " " + std::to_string(best));
+        if (present[p]) fresh.push_back(key + " " + std::to_string(best));
     }
     // nonlinear sub-step: recompute psi in the phase pass (mode 0), or store
     // real-space psi in the density pass (mode 1, with its own variants of the
@@ -1652,18 +1666,25 @@ extern "C" gsn_status gsn_autotune(gsn_grid g, int iters)
         double best_ms = 0.0;
         gsn_status s = time_nonlinear(g, iters, &best_ms);
         if (s) return s;
+        // mode 1: the density pass's variant with the phase pass as it is,
+        // then the phase pass's with the best of those (every pair of the two
+        // would take 36 timings for the same choice)
         const int d0 = g->var[P_DENSITY], h0 = g->var[P_PHASE];
         int bd = d0, bh = h0, bm = 0;
+        double mode1_ms = 1e300;
         g->store_psi = 1;
-        for (int vd = 0; vd < kNumVariants; ++vd)
-            for (int vh = 0; vh < kNumVariants; ++vh) {
+        for (int pass : {P_DENSITY, P_PHASE})
+            for (int v = 0; v < nvar; ++v) {
+                const int vd = pass == P_DENSITY ? v : bd, vh = pass == P_DENSITY ? h0 : v;
+                if (pass == P_PHASE && v == h0) continue;   // timed already
                 g->var[P_DENSITY] = vd;
                 g->var[P_PHASE] = vh;
                 build_schedule(g);
                 double ms = 0.0;
                 if ((s = time_nonlinear(g, iters, &ms))) return s;
-                if (ms < best_ms) { best_ms = ms; bd = vd; bh = vh; bm = 1; }
+                if (ms < mode1_ms) { mode1_ms = ms; bd = vd; bh = vh; }
             }
+        bm = mode1_ms < best_ms;
         g->store_psi = bm;
         g->var[P_DENSITY] = bm ? bd : d0;
         g->var[P_PHASE] = bm ? bh : h0;
@@ -1671,7 +1692,29 @@ extern "C" gsn_status gsn_autotune(gsn_grid g, int iters)
             fresh.push_back(cache_key(g, P_DENSITY) + " " + std::to_string(g->var[P_DENSITY]));
             fresh.push_back(cache_key(g, P_PHASE) + " " + std::to_string(g->var[P_PHASE]));
         }
-        fresh.push_back(mkey + " " + std::to_string(bm));
+        // s4 throughout, by whole steps: on small grids the passes differ by
+        // less than the noise of timing them one by one
+        double chosen_ms = bm ? mode1_ms : best_ms;
+        if (nvar == kNumVariants && from_file == 0) {
+            int keep[P_COUNT];
+            std::copy(g->var, g->var + P_COUNT, keep);
+            for (int p = 0; p < P_COUNT; ++p)
+                if (p != P_ENTRY && p != P_EXIT && present[p]) g->var[p] = kSmallVariant;
+            int mode = -1;
+            for (int m = 0; m < 2; ++m) {
+                g->store_psi = m;
+                build_schedule(g);
+                double ms = 0.0;
+                if ((s = time_nonlinear(g, iters, &ms))) return s;
+                if (ms < chosen_ms) { chosen_ms = ms; mode = m; }
+            }
+            g->store_psi = mode < 0 ? bm : mode;
+            if (mode < 0) std::copy(keep, keep + P_COUNT, g->var);
+            else
+                for (int p = 0; p < P_COUNT; ++p)
+                    if (g->var[p] != keep[p]) fresh.push_back(cache_key(g, p) + " " + std::to_string(g->var[p]));
+        }
+        fresh.push_back(mkey + " " + std::to_string(g->store_psi));
     }
     build_schedule(g);
     if (cpath && *cpath && !fresh.empty()) {

@@ -36,13 +36,15 @@ template <int N, int V> static NKernels make_kernels_c128()
     k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY, D>;
     for (int m = 0; m < 4; ++m) k.lmp[m] = nullptr;
     k.em_pipe = false;
+    if constexpr (V == kSmallVariant) small_kernels<N, D>(k);
     return k;
 }
 
 template <int N> static const NKernels *table_c128(int v)
 {
-    static const NKernels k[3] = {make_kernels_c128<N, 0>(), make_kernels_c128<N, 1>(), make_kernels_c128<N, 4>()};
-    return &k[v == 4 ? 2 : (v & 1)];
+    static const NKernels k[4] = {make_kernels_c128<N, 0>(), make_kernels_c128<N, 1>(), make_kernels_c128<N, 4>(),
+                                  make_kernels_c128<N, kSmallVariant>()};
+    return &k[v >= 4 ? v - 2 : (v & 1)];
 }
 
 const NKernels *kernels_for_c128(int N, int v)

@@ -9,6 +9,7 @@
 
 #include "gsn.h"
 #include "gsn_kernels.hpp"
+#include "gsn_small.hpp"
 
 using namespace gsn;
 
@@ -52,6 +53,8 @@ struct NKernels {
     int lmp_threads = 0;   // their block size when it is not lm_threads()
     // density / phase entries are the pipelined persistent kernels
     bool em_pipe;
+    int em_parts = 1;      // mass partials per block of density / density_store
+    bool mass_block = false;   // strided passes sum the mass partials in a block after their tiles
     int lm_threads() const { return lm_lines * TPL; }
     int em_threads() const { return em_lines * TPL; }
 };
@@ -65,18 +68,20 @@ struct NKernels {
 // budget allows (long lines get 64- or 32-byte segments).  On 512-point lines
 // the strided passes of "p8" run in the two-butterfly form (16 points per
 // thread of the same 8-point plan, two 512-thread blocks per CU, the next tile
-// loaded after the stores), bitwise equal to the one-butterfly form.  The
-// batched solver offers the first kNumBatchVariants.
-constexpr int kNumVariants = 5;
+// loaded after the stores), bitwise equal to the one-butterfly form.  "s4" is
+// the latency form of gsn_small.hpp.  The batched solver offers the first
+// kNumBatchVariants.
+constexpr int kNumVariants = 6;
 constexpr int kNumBatchVariants = 4;
-static const char *kVariantNames[kNumVariants] = {"e16", "e8", "p16", "p8", "s8"};
+constexpr int kSmallVariant = 5;
+static const char *kVariantNames[kNumVariants] = {"e16", "e8", "p16", "p8", "s8", "s4"};
 
 // "s8": 8 points per thread with the smallest tiles that still fill a
 // wavefront (one row pair per block where a row takes 64 threads, four
 // strided lines per block), for grids too small to give every CU a tile.
 template <int N, int V> struct Cfg {
-    static constexpr bool SMALL = V == 4;
-    static constexpr int E0 = (V & 1) || SMALL ? 8 : 16;
+    static constexpr bool SMALL = V == 4, LAT = V == kSmallVariant;
+    static constexpr int E0 = LAT ? SmCfg<N>::E0 : (V & 1) || SMALL ? 8 : 16;
     static constexpr bool PIPE = V == 2 || V == 3;
     static constexpr int E = N < E0 ? N : E0;
     static constexpr int TPL = N / E;
@@ -85,11 +90,30 @@ template <int N, int V> struct Cfg {
     // thread (above that the registers spill), 1024 at 8
     static constexpr int LM_MAXT = E0 >= 16 ? 512 : 1024;
     static constexpr int LM_WANT = TPL <= 4 ? 64 : TPL <= 8 ? 32 : 16;
-    static constexpr int LM_LINES = SMALL ? (TPL >= 16 ? 4 : 64 / TPL)
+    static constexpr int LM_LINES = LAT ? SmCfg<N>::LINES
+                                    : SMALL ? (TPL >= 16 ? 4 : 64 / TPL)
                                           : LM_WANT * TPL <= LM_MAXT ? LM_WANT : LM_MAXT / TPL;
-    static constexpr int EM_LINES = SMALL ? (TPL >= 64 ? 1 : 64 / TPL)
+    static constexpr int EM_LINES = LAT ? SmCfg<N>::WLINES
+                                    : SMALL ? (TPL >= 64 ? 1 : 64 / TPL)
                                           : (256 / TPL) > 64 ? 64 : (256 / TPL) < 1 ? 1 : 256 / TPL;
 };
+
+// The s4 passes of a table (the rest of its entries share the tile shapes).
+template <int N, class ST> void small_kernels(NKernels &k)
+{
+    k.em_fwd = k_sm_em_fft<N, -1, ST>;
+    k.em_inv = k_sm_em_fft<N, 1, ST>;
+    k.density = k_sm_density<N, false, ST>;
+    k.density_store = k_sm_density<N, true, ST>;
+    k.phase = k_sm_phase<N, false, ST>;
+    k.phase_real = k_sm_phase<N, true, ST>;
+    k.lm_fwd = k_sm_lm<N, LM_FWD, ST>;
+    k.lm_inv = k_sm_lm<N, LM_INV, ST>;
+    k.lm_kin = k_sm_lm<N, LM_KIN, ST>;
+    k.lm_kern = k_sm_lm<N, LM_KERN, ST>;
+    k.em_parts = (k.em_threads() + 63) / 64;
+    k.mass_block = true;
+}
 
 // Kernel table of length N, schedule variant v (defined in gsn_api.hip, the
 // only translation unit that instantiates the single-grid kernels of the Kerr

@@ -769,6 +769,9 @@ struct LmArgs {
     DevState *st;
 };
 
+// FP64 sum of the density pass's mass partials, folded into the state (below).
+template <int NT> __device__ __forceinline__ void reduce_mass(const LmArgs &a, double *sh);
+
 template <int N, int E, int LINES, int MODE, class ST>
 __device__ __forceinline__ void lm_tile(const LmArgs &a, int tile_in, ST *lds, double *sh)
 {
@@ -839,17 +842,7 @@ __device__ __forceinline__ void lm_tile(const LmArgs &a, int tile_in, ST *lds, d
             for (int e = 0; e < E; ++e) base[(long long)(t + TPL * e) * sg.es] = st_c<ST>(v[e]);
         }
     }
-    if (a.reduce && tile_in == 0) {
-        double s = 0.0;
-        for (int i = tid; i < a.nmass; i += NT) s += a.mass_parts[i];
-        s = block_sum<NT>(s, sh);
-        if (tid == 0) {
-            a.st->mass_sum = s;
-            a.st->theta += a.k0_dz_over_P * s;
-            a.st->steps += 1;
-            if (!isfinite(s)) a.st->nonfinite = 1;
-        }
-    }
+    if (a.reduce && tile_in == 0) reduce_mass<NT>(a, sh);
 }
 
 // ---------------------------------------------------------------- pipelined LM passes
@@ -1024,7 +1017,18 @@ template <int NT>
 __device__ __forceinline__ void reduce_mass(const LmArgs &a, double *sh)
 {
     double s = 0.0;
-    for (int i = threadIdx.x; i < a.nmass; i += NT) s += gmem(a.mass_parts)[i];
+    const auto p = gmem(a.mass_parts);
+    int i = threadIdx.x;
+    // eight loads in flight per thread: one at a time, the 32768 partials of
+    // 512^3 are 64 memory latencies in a row
+    for (; i + 7 * NT < a.nmass; i += 8 * NT) {
+        double q[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) q[j] = p[i + j * NT];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += q[j];
+    }
+    for (; i < a.nmass; i += NT) s += p[i];
     s = block_sum<NT>(s, sh);
     if (threadIdx.x == 0) {
         auto st = gmem(a.st);
@@ -1065,7 +1069,8 @@ __device__ __forceinline__ void lmp_body(const Src &src, LT *lds, const double2 
             if constexpr (MODE == LM_KERN && TB_L) const_cast<double *>(k2l)[i] = gmem(a0.k2_p)[i];
         }
         if constexpr (!Src::GROUPED) {
-            if (a0.reduce && blockIdx.x == 0) reduce_mass<NT>(a0, sh);
+            // the last block: it never has more tiles than the others
+            if (a0.reduce && blockIdx.x == gridDim.x - 1) reduce_mass<NT>(a0, sh);
         }
     }
     __syncthreads();
@@ -1256,7 +1261,8 @@ __device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *
             if constexpr (MODE == LM_KERN) k2l[i] = gmem(a0.k2_p)[i];
         }
         if constexpr (!Src::GROUPED) {
-            if (a0.reduce && blockIdx.x == 0) reduce_mass<NT>(a0, sh);
+            // the last block: it never has more tiles than the others
+            if (a0.reduce && blockIdx.x == gridDim.x - 1) reduce_mass<NT>(a0, sh);
         }
     }
     __syncthreads();

@@ -58,9 +58,9 @@ template <int N> static const LKernels *local_table(int v)
 {
     // the one-tile kernels of variants 2 and 3 are those of 0 and 1 (same
     // tiles); 2 and 3 add the persistent forms
-    static const LKernels k[5] = {make_local_kernels<N, 0>(), make_local_kernels<N, 1>(),
+    static const LKernels k[kNumVariants] = {make_local_kernels<N, 0>(), make_local_kernels<N, 1>(),
                                   make_local_kernels<N, 2>(), make_local_kernels<N, 3>(),
-                                  make_local_kernels<N, 4>()};
+                                  make_local_kernels<N, 4>(), make_local_kernels<N, kSmallVariant>()};
     return &k[v];
 }
 
