@@ -48,7 +48,7 @@ template <int N, int V> static NKernels make_kernels()
     k.lm_kin = k_lm<N, E, LL, LM_KIN>;
     k.lm_kern = k_lm<N, E, LL, LM_KERN>;
     k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY>;
-    for (int m = 0; m < 4; ++m) k.lmp[m] = nullptr;
+    for (int m = 0; m < 4; ++m) k.lmp[m] = k.lmp2[m] = nullptr;
     k.em_pipe = C::PIPE;
     if constexpr (C::PIPE) {
         k.density = k_densityp<N, E, EL, false>;
@@ -59,14 +59,15 @@ template <int N, int V> static NKernels make_kernels()
         k.lmp[LM_INV] = k_lmp<N, E, LL, LM_INV, float2>;
         k.lmp[LM_KIN] = k_lmp<N, E, LL, LM_KIN, float2>;
         k.lmp[LM_KERN] = k_lmp<N, E, LL, LM_KERN, float2>;
-        // 512-point lines: the two-butterfly form of the same plan (two
-        // blocks per CU instead of one)
-        if constexpr (V == 3 && N == 512) {
-            k.lmp[LM_FWD] = k_lmp2<N, LL, LM_FWD>;
-            k.lmp[LM_INV] = k_lmp2<N, LL, LM_INV>;
-            k.lmp[LM_KIN] = k_lmp2<N, LL, LM_KIN>;
-            k.lmp[LM_KERN] = k_lmp2<N, LL, LM_KERN>;
-            k.lmp_threads = LL * (N / 16);
+        using T = TwoButterfly<N>;
+        if constexpr (V == 3 && T::ON) {
+            k.lmp2[LM_FWD] = k_lmp2<N, T::LINES, LM_FWD>;
+            k.lmp2[LM_INV] = k_lmp2<N, T::LINES, LM_INV>;
+            k.lmp2[LM_KIN] = k_lmp2<N, T::LINES, LM_KIN>;
+            k.lmp2[LM_KERN] = k_lmp2<N, T::LINES, LM_KERN>;
+            k.lmp2_lines = T::LINES;
+            k.lmp2_threads = T::THREADS;
+            k.lmp2_min_tiles = T::MIN_TILES;
         }
     }
     if constexpr (V == kSmallVariant) small_kernels<N, float2>(k);
@@ -320,21 +321,45 @@ int persistent_blocks(const void *fn, int threads)
     return n;
 }
 
-static Launch lm_launch(void (*fn)(LmArgs), const NKernels *k, const LmArgs &a, int pass)
+// The same lines in tiles of `lines`.
+static void regroup(Seg &s, int lines)
+{
+    if (s.ntiles == 0) return;
+    const int nouter = s.ntiles / s.ngroups;
+    s.ngroups = (s.nlines + lines - 1) / lines;
+    s.ntiles = s.ngroups * nouter;
+}
+
+static Launch lm_launch(void (*fn)(LmArgs), const NKernels *k, LmArgs a, int pass)
 {
     Launch L;
     std::memset(&L, 0, sizeof(L));
-    const int ntiles = a.s0.ntiles + a.s1.ntiles;
     int mode = -1;
     if (fn == k->lm_fwd) mode = LM_FWD;
     else if (fn == k->lm_inv) mode = LM_INV;
     else if (fn == k->lm_kin) mode = LM_KIN;
     else if (fn == k->lm_kern) mode = LM_KERN;
     const int N = k->E * k->TPL;
-    int grid = ntiles, threads = k->lm_threads();
-    if (mode >= 0 && k->lmp[mode] && lm_fits(a.s0, N, k->lm_lines) && lm_fits(a.s1, N, k->lm_lines)) {
+    int threads = k->lm_threads();
+    bool pipe = false;
+    if (mode >= 0 && k->lmp2[mode] && lm_fits(a.s0, N, k->lmp2_lines) && lm_fits(a.s1, N, k->lmp2_lines)) {
+        Seg s0 = a.s0, s1 = a.s1;
+        regroup(s0, k->lmp2_lines);
+        regroup(s1, k->lmp2_lines);
+        if (s0.ntiles + s1.ntiles >= k->lmp2_min_tiles) {
+            a.s0 = s0;
+            a.s1 = s1;
+            fn = k->lmp2[mode];
+            threads = k->lmp2_threads;
+            pipe = true;
+        }
+    }
+    if (!pipe && mode >= 0 && k->lmp[mode] && lm_fits(a.s0, N, k->lm_lines) && lm_fits(a.s1, N, k->lm_lines)) {
         fn = k->lmp[mode];
-        if (k->lmp_threads > 0) threads = k->lmp_threads;
+        pipe = true;
+    }
+    int grid = a.s0.ntiles + a.s1.ntiles;
+    if (pipe) {
         const int pb = persistent_blocks((const void *)fn, threads);
         if (pb > 0 && pb < grid) grid = pb;
     }

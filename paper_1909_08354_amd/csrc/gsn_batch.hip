@@ -189,7 +189,8 @@ struct GKernels {
     const void *em_fwd, *em_inv;
     const void *density, *density_store, *phase, *phase_real;
     const void *lm_kin, *lm_kern;
-    int lm_threads() const { return lm_lines * TPL; }
+    int lm_nt;   // threads of a strided block
+    int lm_threads() const { return lm_nt; }
     int em_threads() const { return em_lines * TPL; }
 };
 
@@ -201,6 +202,7 @@ template <int N, int V> GKernels make_gkernels()
     k.E = E;
     k.TPL = C::TPL;
     k.lm_lines = LL;
+    k.lm_nt = LL * C::TPL;
     k.em_lines = EL;
     k.pipe = C::PIPE;
     k.em_fwd = (const void *)k_em_fft_g<N, E, EL, -1>;
@@ -212,6 +214,13 @@ template <int N, int V> GKernels make_gkernels()
         k.phase_real = (const void *)k_phasep_g<N, E, EL, true>;
         k.lm_kin = (const void *)k_lmp_g<N, E, LL, LM_KIN>;
         k.lm_kern = (const void *)k_lmp_g<N, E, LL, LM_KERN>;
+        using T = TwoButterfly<N>;
+        if constexpr (V == 3 && T::BATCH) {
+            k.lm_kin = (const void *)k_lmp2_g<N, T::LINES, LM_KIN>;
+            k.lm_kern = (const void *)k_lmp2_g<N, T::LINES, LM_KERN>;
+            k.lm_lines = T::LINES;
+            k.lm_nt = T::THREADS;
+        }
     } else {
         k.density = (const void *)k_density_g<N, E, EL, false>;
         k.density_store = (const void *)k_density_g<N, E, EL, true>;

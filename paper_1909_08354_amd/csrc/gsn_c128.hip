@@ -34,7 +34,7 @@ template <int N, int V> static NKernels make_kernels_c128()
     k.lm_kin = k_lm<N, E, LL, LM_KIN, D>;
     k.lm_kern = k_lm<N, E, LL, LM_KERN, D>;
     k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY, D>;
-    for (int m = 0; m < 4; ++m) k.lmp[m] = nullptr;
+    for (int m = 0; m < 4; ++m) k.lmp[m] = k.lmp2[m] = nullptr;
     k.em_pipe = false;
     if constexpr (V == kSmallVariant) small_kernels<N, D>(k);
     return k;

@@ -46,106 +46,117 @@ template <int S> __device__ __forceinline__ dc mul_si(dc a)
     else return mk(a.y, -a.x);
 }
 
-// cos and sin of 2 pi m / 16 (exact mathematical constants)
+// cos(pi/8), sin(pi/8), sqrt(1/2)
 constexpr double kC1 = 0.92387953251128675613;  // cos(pi/8)
 constexpr double kS1 = 0.38268343236508977173;  // sin(pi/8)
 constexpr double kR2 = 0.70710678118654752440;  // sqrt(1/2)
 
-// a * exp(S 2 pi i m / 16) for a compile-time m in [0, 16)
-template <int S, int M> __device__ __forceinline__ dc tw16(dc a)
+// p + w q and p - w q in six FMAs: the difference is 2 p minus the sum.
+__device__ __forceinline__ void bfly(dc &p, dc &q, dc w)
 {
-    constexpr int m = M & 15;
-    if constexpr (m == 0) return a;
-    else if constexpr (m == 4) return mul_si<S>(a);
-    else if constexpr (m == 8) return mk(-a.x, -a.y);
-    else if constexpr (m == 12) return mul_si<-S>(a);
-    else if constexpr (m == 2 || m == 6 || m == 10 || m == 14) {
-        // (cx, S*sy) with |cx| = |sy| = sqrt(1/2)
-        constexpr double cx = (m == 2 || m == 14) ? kR2 : -kR2;
-        constexpr double sy = (m == 2 || m == 6) ? kR2 : -kR2;
-        constexpr double ss = S > 0 ? sy : -sy;
-        return mk(cx * a.x - ss * a.y, cx * a.y + ss * a.x);
-    } else {
-        constexpr double c = (m == 1 || m == 15) ? kC1 : (m == 3 || m == 13) ? kS1
-                           : (m == 5 || m == 11) ? -kS1 : -kC1;
-        constexpr double s0 = (m == 1 || m == 7) ? kS1 : (m == 3 || m == 5) ? kC1
-                            : (m == 9 || m == 15) ? -kS1 : -kC1;
-        constexpr double s = S > 0 ? s0 : -s0;
-        return mk(fma(c, a.x, -s * a.y), fma(c, a.y, s * a.x));
-    }
+    const dc s = mk(fma(w.x, q.x, fma(-w.y, q.y, p.x)), fma(w.x, q.y, fma(w.y, q.x, p.y)));
+    q = mk(fma(2.0, p.x, -s.x), fma(2.0, p.y, -s.y));
+    p = s;
+}
+__device__ __forceinline__ void bfly(dc &p, dc &q)
+{
+    const dc s = add(p, q);
+    q = sub(p, q);
+    p = s;
 }
 
-template <int S> __device__ __forceinline__ void dft2(dc *a)
+// a +- c u (real c)
+__device__ __forceinline__ dc axpy(double c, dc u, dc a) { return mk(fma(c, u.x, a.x), fma(c, u.y, a.y)); }
+
+// DFT4 outputs from the first layer's sums and differences of the points 0, 2
+// (s02, d02) and 1, 3 (s13, d13)
+template <int S>
+__device__ __forceinline__ void dft4_out(dc s02, dc s13, dc d02, dc d13, dc &x0, dc &x1, dc &x2, dc &x3)
 {
-    dc t = a[0];
-    a[0] = add(t, a[1]);
-    a[1] = sub(t, a[1]);
+    const dc r = mul_si<S>(d13);
+    x0 = add(s02, s13);
+    x2 = sub(s02, s13);
+    x1 = add(d02, r);
+    x3 = sub(d02, r);
 }
 
-template <int S> __device__ __forceinline__ void dft4(dc &a0, dc &a1, dc &a2, dc &a3)
+// The same when the points 1 and 3 are c times those of s13 and d13
+template <int S>
+__device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d02, dc d13, dc &x0, dc &x1, dc &x2, dc &x3)
 {
-    dc s02 = add(a0, a2), d02 = sub(a0, a2);
-    dc s13 = add(a1, a3), d13 = mul_si<S>(sub(a1, a3));
-    a0 = add(s02, s13);
-    a2 = sub(s02, s13);
-    a1 = add(d02, d13);
-    a3 = sub(d02, d13);
+    const dc r = mul_si<S>(d13);
+    x0 = axpy(c, s13, s02);
+    x2 = axpy(-c, s13, s02);
+    x1 = axpy(c, r, d02);
+    x3 = axpy(-c, r, d02);
 }
 
-template <int S> __device__ __forceinline__ void dft4(dc *a) { dft4<S>(a[0], a[1], a[2], a[3]); }
-
-// length-8 DFT: even/odd split into two length-4 DFTs
-template <int S> __device__ __forceinline__ void dft8(dc *a)
+// Length-R DFT in registers, natural order in and out; TW: point r is first
+// multiplied by w(r) (r >= 1).  The FFT passes are bound by FP64 issue (a
+// 256-point kinetic pass issues for 95% of its time), so the multiplications
+// go into the additions that follow them: a twiddled first-layer pair takes
+// 10 instructions instead of 12 (6 instead of 8 for point 0), and a constant
+// rotation is applied as c (1, tan) with c folded into the next layer's FMAs
+// (cos pi/8 or sqrt(1/2); the tangent never exceeds 1).
+template <int R, int S, bool TW, class W> __device__ __forceinline__ void dft(dc *a, const W &w)
 {
-    dc e0 = a[0], e1 = a[2], e2 = a[4], e3 = a[6];
-    dc o0 = a[1], o1 = a[3], o2 = a[5], o3 = a[7];
-    dft4<S>(e0, e1, e2, e3);
-    dft4<S>(o0, o1, o2, o3);
-    o1 = tw16<S, 2>(o1);
-    o2 = tw16<S, 4>(o2);
-    o3 = tw16<S, 6>(o3);
-    a[0] = add(e0, o0); a[4] = sub(e0, o0);
-    a[1] = add(e1, o1); a[5] = sub(e1, o1);
-    a[2] = add(e2, o2); a[6] = sub(e2, o2);
-    a[3] = add(e3, o3); a[7] = sub(e3, o3);
-}
-
-// length-16 DFT as 4 x 4: Y_q = DFT4(a_q, a_{q+4}, a_{q+8}, a_{q+12}),
-// Y_q[k] *= w16^{q k}, X_{k + 4 j} = DFT4_q(Y_q[k])[j]
-template <int S> __device__ __forceinline__ void dft16(dc *a)
-{
-    dc y[16];
+    static_assert(R == 1 || R == 2 || R == 4 || R == 8 || R == 16, "unsupported radix");
+    if constexpr (R > 1) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        dc b0 = a[q], b1 = a[q + 4], b2 = a[q + 8], b3 = a[q + 12];
-        dft4<S>(b0, b1, b2, b3);
-        y[q * 4 + 0] = b0; y[q * 4 + 1] = b1; y[q * 4 + 2] = b2; y[q * 4 + 3] = b3;
+        for (int i = 0; i < R / 2; ++i) {
+            if constexpr (TW) {
+                if (i > 0) a[i] = cmul(a[i], w(i));
+                bfly(a[i], a[i + R / 2], w(i + R / 2));
+            } else {
+                bfly(a[i], a[i + R / 2]);
+            }
+        }
     }
-    // twiddles w16^{q k}
-    y[1 * 4 + 1] = tw16<S, 1>(y[5]);
-    y[1 * 4 + 2] = tw16<S, 2>(y[6]);
-    y[1 * 4 + 3] = tw16<S, 3>(y[7]);
-    y[2 * 4 + 1] = tw16<S, 2>(y[9]);
-    y[2 * 4 + 2] = tw16<S, 4>(y[10]);
-    y[2 * 4 + 3] = tw16<S, 6>(y[11]);
-    y[3 * 4 + 1] = tw16<S, 3>(y[13]);
-    y[3 * 4 + 2] = tw16<S, 6>(y[14]);
-    y[3 * 4 + 3] = tw16<S, 9>(y[15]);
+    if constexpr (R == 4) {
+        dft4_out<S>(a[0], a[1], a[2], a[3], a[0], a[1], a[2], a[3]);
+    } else if constexpr (R == 8) {
+        // even and odd points, then X[k] = E[k] + w8^k O[k], X[k + 4] = E[k] - w8^k O[k]
+        dc e0, e1, e2, e3, o0, o1, o2, o3;
+        dft4_out<S>(a[0], a[2], a[4], a[6], e0, e1, e2, e3);
+        dft4_out<S>(a[1], a[3], a[5], a[7], o0, o1, o2, o3);
+        // w8 = sqrt(1/2) (1 + S i), w8^3 = sqrt(1/2) (-1 + S i)
+        const dc r1 = mul_si<S>(o1), r2 = mul_si<S>(o2), r3 = mul_si<S>(o3);
+        const dc u1 = add(o1, r1), u3 = sub(r3, o3);
+        a[0] = add(e0, o0); a[4] = sub(e0, o0);
+        a[1] = axpy(kR2, u1, e1); a[5] = axpy(-kR2, u1, e1);
+        a[2] = add(e2, r2); a[6] = sub(e2, r2);
+        a[3] = axpy(kR2, u3, e3); a[7] = axpy(-kR2, u3, e3);
+    } else if constexpr (R == 16) {
+        // 4 x 4: Y_q = DFT4 of the points q, q + 4, q + 8, q + 12;
+        // X[k + 4 j] = DFT4 over q of w16^(q k) Y_q[k]
+        dc y[4][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        dc b0 = y[k], b1 = y[4 + k], b2 = y[8 + k], b3 = y[12 + k];
-        dft4<S>(b0, b1, b2, b3);
-        a[k] = b0; a[k + 4] = b1; a[k + 8] = b2; a[k + 12] = b3;
+        for (int q = 0; q < 4; ++q)
+            dft4_out<S>(a[q], a[q + 4], a[q + 8], a[q + 12], y[q][0], y[q][1], y[q][2], y[q][3]);
+        bfly(y[0][0], y[2][0]);
+        bfly(y[1][0], y[3][0]);
+        dft4_out<S>(y[0][0], y[1][0], y[2][0], y[3][0], a[0], a[4], a[8], a[12]);
+        constexpr double t = kS1 / kC1;   // tan(pi/8)
+        {   // k = 1: angles pi/8, pi/4, 3 pi/8
+            const dc v = y[1][1], u1 = mk(fma(-S * t, v.y, v.x), fma(S * t, v.x, v.y));
+            const dc u3 = mk(fma(t, y[3][1].x, -S * y[3][1].y), fma(t, y[3][1].y, S * y[3][1].x));
+            const dc u2 = add(y[2][1], mul_si<S>(y[2][1]));
+            dft4_out<S>(kC1, axpy(kR2, u2, y[0][1]), add(u1, u3), axpy(-kR2, u2, y[0][1]), sub(u1, u3), a[1], a[5],
+                        a[9], a[13]);
+        }
+        {   // k = 2: pi/4, pi/2, 3 pi/4
+            const dc u1 = add(y[1][2], mul_si<S>(y[1][2])), u3 = sub(mul_si<S>(y[3][2]), y[3][2]);
+            const dc b2 = mul_si<S>(y[2][2]);
+            dft4_out<S>(kR2, add(y[0][2], b2), add(u1, u3), sub(y[0][2], b2), sub(u1, u3), a[2], a[6], a[10], a[14]);
+        }
+        {   // k = 3: 3 pi/8, 3 pi/4, 9 pi/8
+            const dc u1 = mk(fma(t, y[1][3].x, -S * y[1][3].y), fma(t, y[1][3].y, S * y[1][3].x));
+            const dc u2 = sub(mul_si<S>(y[2][3]), y[2][3]);
+            const dc v = y[3][3], u3 = mk(fma(S * t, v.y, -v.x), fma(-S * t, v.x, -v.y));
+            dft4_out<S>(kC1, axpy(kR2, u2, y[0][3]), add(u1, u3), axpy(-kR2, u2, y[0][3]), sub(u1, u3), a[3], a[7],
+                        a[11], a[15]);
+        }
     }
-}
-
-template <int R, int S> __device__ __forceinline__ void dft(dc *a)
-{
-    if constexpr (R == 2) dft2<S>(a);
-    else if constexpr (R == 4) dft4<S>(a);
-    else if constexpr (R == 8) dft8<S>(a);
-    else if constexpr (R == 16) dft16<S>(a);
-    else static_assert(R == 1, "unsupported radix");
 }
 
 // Stage plan: ceil(log_E N) stages, the first of radix N / E^(stages - 1)
@@ -214,6 +225,17 @@ template <int LINES> struct LmLayout {
     __device__ __forceinline__ int operator()(int pos) const { return pos * LINES + l; }
 };
 
+// The twiddles of butterfly jm of a stage: w(r) = exp(S 2 pi i jm r STEP / N).
+template <int STEP, int S> struct Twiddles {
+    const double2 *__restrict__ tw;
+    int jm;
+    __device__ __forceinline__ dc operator()(int r) const
+    {
+        const double2 w = tw[jm * r * STEP];
+        return mk(w.x, S > 0 ? -w.y : w.y);
+    }
+};
+
 // One Stockham stage and the recursion over the remaining stages.
 template <int N, int E, int S, int ST, class Lay, class LT>
 __device__ __forceinline__ void fft_stages(dc (&v)[E], int t, const Lay &lay, LT *lds,
@@ -232,17 +254,7 @@ __device__ __forceinline__ void fft_stages(dc (&v)[E], int t, const Lay &lay, LT
             dc a[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) a[r] = v[m + r * B];
-            if constexpr (NS > 1) {
-                const int jm = j & (NS - 1);
-                constexpr int STEP = N / (NS * R);
-#pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    dc w = from_d2(tw[jm * r * STEP]);
-                    if constexpr (S > 0) w.y = -w.y;
-                    a[r] = cmul(a[r], w);
-                }
-            }
-            dft<R, S>(a);
+            dft<R, S, (NS > 1)>(a, Twiddles<N / (NS * R), S>{tw, j & (NS - 1)});
             if constexpr (LAST) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) v[m + r * B] = a[r];

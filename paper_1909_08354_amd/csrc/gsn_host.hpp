@@ -50,7 +50,10 @@ struct NKernels {
     void (*lm_kin_energy)(LmArgs);
     // pipelined persistent forms of LM_FWD .. LM_KERN (null: not in this variant)
     void (*lmp[4])(LmArgs);
-    int lmp_threads = 0;   // their block size when it is not lm_threads()
+    // the two-butterfly forms of the same passes (null: none), their lines per
+    // tile and the tiles a pass must have for them
+    void (*lmp2[4])(LmArgs);
+    int lmp2_lines = 0, lmp2_threads = 0, lmp2_min_tiles = 0;
     // density / phase entries are the pipelined persistent kernels
     bool em_pipe;
     int em_parts = 1;      // mass partials per block of density / density_store
@@ -65,10 +68,10 @@ struct NKernels {
 // "s8" is the small-tile form for small grids.  The EM tile holds
 // 256/TPL rows (at most 64); the LM tile holds LINES columns chosen so that a
 // tile moves 128-byte contiguous segments per row where the block's thread
-// budget allows (long lines get 64- or 32-byte segments).  On 512-point lines
-// the strided passes of "p8" run in the two-butterfly form (16 points per
-// thread of the same 8-point plan, two 512-thread blocks per CU, the next tile
-// loaded after the stores), bitwise equal to the one-butterfly form.  "s4" is
+// budget allows (long lines get 64- or 32-byte segments).  On lines of 256
+// points and more the strided passes of "p8" run in the two-butterfly form (16
+// points per thread of the same 8-point plan, the next tile loaded after the
+// stores), bitwise equal to the one-butterfly form.  "s4" is
 // the latency form of gsn_small.hpp.  The batched solver offers the first
 // kNumBatchVariants.
 constexpr int kNumVariants = 6;
@@ -96,6 +99,20 @@ template <int N, int V> struct Cfg {
     static constexpr int EM_LINES = LAT ? SmCfg<N>::WLINES
                                     : SMALL ? (TPL >= 64 ? 1 : 64 / TPL)
                                           : (256 / TPL) > 64 ? 64 : (256 / TPL) < 1 ? 1 : 256 / TPL;
+};
+
+// The strided passes of p8 in the two-butterfly form (k_lmp2): 256-point lines
+// and longer, in tiles of LINES lines -- 128-byte row segments where a block of
+// 1024 threads holds them.  1024-point tiles of 16 lines take a whole CU and
+// need the pass to hold one for every CU: on 2^26 points the y kinetic pass
+// takes 380 us with them and 443 with 8-line tiles, but on 1024 x 2048 (128
+// tiles) 25 us and 20.  A batch keeps the 8-line tiles (21 x 1024^2: 482
+// against 487 us a step).  The results are the same bits either way.
+template <int N> struct TwoButterfly {
+    static constexpr bool ON = N >= 256, BATCH = ON && N != 1024;
+    static constexpr int LINES = N >= 2048 ? 8 : 16;
+    static constexpr int THREADS = LINES * (N / 16);
+    static constexpr int MIN_TILES = N == 1024 ? 256 : 0;
 };
 
 // The s4 passes of a table (the rest of its entries share the tile shapes).

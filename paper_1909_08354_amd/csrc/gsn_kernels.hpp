@@ -929,6 +929,13 @@ __device__ __forceinline__ LmWhere lm_where(const LmArgs &a, int tile, int l, in
     return w;
 }
 
+// The thread's place in its line, opaque to the compiler from here on: in a
+// loop over tiles, what is derived from it (LDS addresses of every stage) is
+// computed again per tile instead of being kept in registers across the loop.
+// At 16 points per thread of a 1024-point line that is the difference between
+// 42 spilled registers and none.
+__device__ __forceinline__ void hide(int &t) { asm volatile("" : "+v"(t)); }
+
 // An empty asm that takes x as input and output: code that computes x stays
 // before this point.
 __device__ __forceinline__ void pin(dc &x) { asm volatile("" : "+v"(x.x), "+v"(x.y)); }
@@ -945,6 +952,19 @@ template <int E> struct LmPrefetch {
     double q1, q2;    // |k|^2 parts k2_1[c1], k2_2[c2]
 };
 
+// The loads of a tile's line factors.
+template <int MODE, class F>
+__device__ __forceinline__ void lm_fetch_line(const LmArgs &a, const LmWhere &w, bool live, F &f)
+{
+    if constexpr (MODE == LM_KIN) {
+        f.f1 = gld(a.kin1, live ? w.c1 : 0);
+        f.f2 = gld(a.kin2, live ? w.c2 : 0);
+    } else if constexpr (MODE == LM_KERN) {
+        f.q1 = gmem(a.k2_1)[live ? w.c1 : 0];
+        f.q2 = gmem(a.k2_2)[live ? w.c2 : 0];
+    }
+}
+
 // Issue the loads of one tile.  live = false (no tile left): every lane loads
 // the tile base point E times instead, so the count of vector-memory
 // operations per iteration stays fixed and costs one cache line.
@@ -954,13 +974,7 @@ __device__ __forceinline__ void lm_fetch(const LmArgs &a, const LmWhere &w, bool
     const unsigned vo = live ? w.voff : 0u, st = live ? w.step : 0u;
 #pragma unroll
     for (int e = 0; e < E; ++e) f.p[e] = buf_ld2(w.r, vo, e * st);
-    if constexpr (MODE == LM_KIN) {
-        f.f1 = gld(a.kin1, live ? w.c1 : 0);
-        f.f2 = gld(a.kin2, live ? w.c2 : 0);
-    } else if constexpr (MODE == LM_KERN) {
-        f.q1 = gmem(a.k2_1)[live ? w.c1 : 0];
-        f.q2 = gmem(a.k2_2)[live ? w.c2 : 0];
-    }
+    lm_fetch_line<MODE>(a, w, live, f);
 }
 
 // Where the tiles of a pipelined pass come from: one grid (tile t of its
@@ -1149,70 +1163,56 @@ __device__ __forceinline__ void lmp_body(const Src &src, LT *lds, const double2 
 }
 
 // ---------------------------------------------------------------- two-butterfly LM pass
-// The persistent strided pass for lines of N = 8^S points with 16 points per
-// thread: each thread runs two radix-8 butterflies per stage, so a 16-line
-// tile of 512-point lines takes 512 threads.  Between stages the values stay
-// in registers as the complex64 numbers the LDS exchange holds (widened to
-// FP64 one butterfly at a time); the forward transform's last stage, the
-// pointwise multiplier and the inverse transform's first stage run back to
-// back per butterfly in FP64, and the last stage stores its outputs directly.
-// At N = 512 a thread then fits 128 VGPRs and a block's LDS (tile, twiddles,
-// per-axis table) 80 KiB, so two blocks share a CU and one block's barriers
-// and memory waits are covered by the other's work; the next tile is loaded
-// after the stores, not prefetched.  Every butterfly, twiddle and rounding
-// point is that of the 8-point plan (Plan<N, 8>), so the results are bitwise
-// those of the one-butterfly passes k_lm / k_lmp with E = 8.
+// The persistent strided pass with 16 points per thread of the 8-point plan
+// (radices R0, 8, .., 8): each thread runs 16 / R butterflies per stage, so a
+// 16-line tile of 512-point lines takes 512 threads, one of 1024 points 1024.
+// Between stages the values stay in registers as the complex64 numbers the LDS
+// exchange holds (widened to FP64 one butterfly at a time); the forward
+// transform's last stage, the pointwise multiplier and the inverse transform's
+// first stage run back to back per butterfly in FP64, and the last stage
+// stores its outputs directly.  A thread then fits 128 VGPRs, so four waves
+// share a SIMD: at N = 512 two blocks of 80 KiB of LDS (tile, twiddles,
+// per-axis table) per CU, and one block's barriers and memory waits are
+// covered by the other's work; the next tile is loaded after the stores.
+// (Loading it before them, into the registers the last stage has read, was
+// slower: the z kinetic pass of 512^3 took 757 us instead of 671.)  Every
+// butterfly, twiddle and rounding point is that of Plan<N, 8>, so the results
+// are bitwise those of the one-butterfly passes k_lm / k_lmp with E = 8.
+// Measured against those, 8-line tiles at 1024 and 4-line tiles at 2048 points:
+// y kinetic pass of 256 x 1024 x 256 380 us (443), columns of 2048^2 29 us
+// (38-42), y transform of 256^3 23.5 us (26.4).
 template <int N> struct R8 {
     static constexpr int E = 16, TPL = N / E;
-    static constexpr int stages()
-    {
-        int s = 0;
-        long p = 1;
-        while (p < N) { p *= 8; ++s; }
-        return s;
-    }
-    static constexpr bool POW8 = [] { long p = 1; while (p < N) p *= 8; return p == N; }();
-    static constexpr int ns(int st)
-    {
-        int p = 1;
-        for (int i = 0; i < st; ++i) p *= 8;
-        return p;
-    }
+    using P = Plan<N, 8>;
+    static constexpr int stages() { return P::nstages(); }
+    static constexpr int radix(int st) { return P::radix(st); }
+    static constexpr int ns(int st) { return P::ns(st); }
     // twiddle indices (j mod Ns) r N / (8 Ns) stay below this
     static constexpr int TWN = (N / 8 - 1) * 7 + 1;
 };
 
-// Butterfly m (0 or 1) of stage ST: j = t + TPL m takes positions j + r N / 8,
-// held in u[m + 2 r]; twiddled and transformed in FP64 into a.
-template <int N, int S, int ST>
-__device__ __forceinline__ void r8_in(const float2 (&u)[16], int m, int t, const double2 *__restrict__ tw, dc (&a)[8])
+// Butterfly m of stage ST (radix R): j = t + TPL m takes positions j + r N / R,
+// held in u[m + r 16 / R]; twiddled and transformed in FP64 into a.
+template <int N, int S, int ST, int R>
+__device__ __forceinline__ void r8_in(const float2 (&u)[16], int m, int t, const double2 *__restrict__ tw, dc (&a)[R])
 {
-    constexpr int NS = R8<N>::ns(ST), STEP = N / (NS * 8);
+    static_assert(R == R8<N>::radix(ST), "radix");
+    constexpr int NS = R8<N>::ns(ST), STEP = N / (NS * R);
     const int j = t + R8<N>::TPL * m;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) a[r] = from_f2(u[m + 2 * r]);
-    if constexpr (NS > 1) {
-        const int jm = j & (NS - 1);
-#pragma unroll
-        for (int r = 1; r < 8; ++r) {
-            dc w = from_d2(tw[jm * r * STEP]);
-            if constexpr (S > 0) w.y = -w.y;
-            a[r] = cmul(a[r], w);
-        }
-    }
-    dft<8, S>(a);
+    for (int r = 0; r < R; ++r) a[r] = from_f2(u[m + r * (16 / R)]);
+    dft<R, S, (NS > 1)>(a, Twiddles<STEP, S>{tw, j & (NS - 1)});
 }
 
-// Outputs of butterfly m of a stage that is not the last: LDS positions
+// Outputs of butterfly j of a stage that is not the last: LDS positions
 // expand(j) + r Ns.
-template <int N, int ST, class Lay>
-__device__ __forceinline__ void r8_out(const dc (&a)[8], int m, int t, const Lay &lay, float2 *lds)
+template <int N, int ST, int R, class Lay>
+__device__ __forceinline__ void r8_out(const dc (&a)[R], int j, const Lay &lay, float2 *lds)
 {
     constexpr int NS = R8<N>::ns(ST);
-    const int j = t + R8<N>::TPL * m;
-    const int base = (j / NS) * NS * 8 + (j & (NS - 1));
+    const int base = (j / NS) * NS * R + (j & (NS - 1));
 #pragma unroll
-    for (int r = 0; r < 8; ++r) lds_put(lds, lay(base + r * NS), a[r]);
+    for (int r = 0; r < R; ++r) lds_put(lds, lay(base + r * NS), a[r]);
 }
 
 // The exchange after a stage: u[e] takes position t + TPL e.
@@ -1231,11 +1231,12 @@ __device__ __forceinline__ void r8_stages(float2 (&u)[16], int t, const Lay &lay
                                           const double2 *__restrict__ tw)
 {
     if constexpr (ST < STOP) {
+        constexpr int R = R8<N>::radix(ST);
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            dc a[8];
+        for (int m = 0; m < 16 / R; ++m) {
+            dc a[R];
             r8_in<N, S, ST>(u, m, t, tw, a);
-            r8_out<N, ST>(a, m, t, lay, lds);
+            r8_out<N, ST>(a, t + R8<N>::TPL * m, lay, lds);
         }
         r8_exchange<N>(u, t, lay, lds);
         r8_stages<N, S, ST + 1, STOP>(u, t, lay, lds, tw);
@@ -1244,21 +1245,22 @@ __device__ __forceinline__ void r8_stages(float2 (&u)[16], int t, const Lay &lay
 
 __device__ __forceinline__ void pin_f2(float2 &x) { asm volatile("" : "+v"(x.x), "+v"(x.y)); }
 
-template <int N, int LINES, int MODE, class Src>
-__device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *twl, double2 *kpl, double *k2l,
-                                          double *sh)
+template <int N, int LINES, int MODE, class Src, bool TB_L = true>
+__device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *twl, const double2 *kpl,
+                                          const double *k2l, double *sh)
 {
     using P = R8<N>;
     constexpr int E = P::E, TPL = P::TPL, NT = LINES * TPL, LAST = P::stages() - 1;
-    static_assert(P::POW8 && LAST >= 1, "two-butterfly pass: N = 8^S, S >= 2");
+    static_assert(P::radix(LAST) == 8 && LAST >= 1, "two-butterfly pass: a last radix of 8");
     static_assert(MODE == LM_FWD || MODE == LM_INV || MODE == LM_KIN || MODE == LM_KERN, "mode");
-    const int tid = threadIdx.x, l = tid % LINES, t = tid / LINES;
+    const int tid = threadIdx.x, l = tid % LINES;
+    int t = tid / LINES;
     {
         const LmArgs &a0 = src.args(0);
         for (int i = tid; i < N; i += NT) {
             if (i < P::TWN) twl[i] = gld(a0.tw, i);
-            if constexpr (MODE == LM_KIN) kpl[i] = gld(a0.kinp, i);
-            if constexpr (MODE == LM_KERN) k2l[i] = gmem(a0.k2_p)[i];
+            if constexpr (MODE == LM_KIN && TB_L) const_cast<double2 *>(kpl)[i] = gld(a0.kinp, i);
+            if constexpr (MODE == LM_KERN && TB_L) const_cast<double *>(k2l)[i] = gmem(a0.k2_p)[i];
         }
         if constexpr (!Src::GROUPED) {
             // the last block: it never has more tiles than the others
@@ -1280,6 +1282,7 @@ __device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *
     if constexpr (MODE == LM_KIN) m12 = scl(cmul(from_d2(f.f1), from_d2(f.f2)), src.args(tile).scale);
     if constexpr (MODE == LM_KERN) q12 = f.q1 + f.q2;
     for (;;) {
+        if constexpr (N >= 1024) hide(t);
         const LmArgs &a = src.args(tile);
         const int nxt = tile + gridDim.x;
         const bool more = nxt < ntiles;
@@ -1319,8 +1322,17 @@ __device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *
                         z[r] = scl(z[r], K * a.scale);
                     }
                 }
-                dft<8, 1>(z);
-                r8_out<N, 0>(z, m, t, lay, lds);
+                // the inverse's first stage (radix R0, no twiddles): this
+                // butterfly's bins hold 8 / R0 of its butterflies
+                constexpr int R0 = P::radix(0), Q = 8 / R0;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    dc y[R0];
+#pragma unroll
+                    for (int i = 0; i < R0; ++i) y[i] = z[q + i * Q];
+                    dft<R0, 1, false>(y, 0);
+                    r8_out<N, 0>(y, j + q * (N / 8), lay, lds);
+                }
             }
             r8_exchange<N>(u, t, lay, lds);
             r8_stages<N, 1, 1, LAST>(u, t, lay, lds, twl);
@@ -1507,7 +1519,8 @@ template <int N, int E, int LINES, bool REAL_IN, class LT, class Src>
 __device__ __forceinline__ void phasep_body(const Src &src, LT *lds, double2 *twl, double2 *scl_tab)
 {
     constexpr int TPL = N / E, NT = LINES * TPL;
-    const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
+    const int tid = threadIdx.x, l = tid / TPL;
+    int t = tid % TPL;
     for (int i = tid; i < kSinCosTable; i += NT) scl_tab[i] = gld(src.args(0).sct, i);
     copy_twiddles<N, E, LINES>(src.args(0).tw, twl);
     const int ntiles = src.ntiles();
@@ -1527,6 +1540,7 @@ __device__ __forceinline__ void phasep_body(const Src &src, LT *lds, double2 *tw
     dc z[E];
     em_build_z<N, E>(fp, t, z);
     for (;;) {
+        if constexpr (E == 8) hide(t);
         const EmArgs &a = src.args(tile);
         const int nxt = tile + gridDim.x;
         const bool more = nxt < ntiles;
@@ -1581,7 +1595,8 @@ __device__ __forceinline__ void phasep_local_body(const Src &src, LT *lds, doubl
                                                   float *stash)
 {
     constexpr int TPL = N / E, NT = LINES * TPL;
-    const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
+    const int tid = threadIdx.x, l = tid / TPL;
+    int t = tid % TPL;
     for (int i = tid; i < kSinCosTable; i += NT) scl_tab[i] = gld(src.args(0).sct, i);
     copy_twiddles<N, E, LINES>(src.args(0).tw, twl);
     const int ntiles = src.ntiles();
@@ -1602,6 +1617,7 @@ __device__ __forceinline__ void phasep_local_body(const Src &src, LT *lds, doubl
     dc z[E];
     em_build_z<N, E>(fp, t, z);
     for (;;) {
+        if constexpr (E == 8) hide(t);
         const EmArgs &a = src.args(tile);
         const int nxt = tile + gridDim.x;
         const bool more = nxt < ntiles;
@@ -1698,7 +1714,8 @@ template <int N, int E, int LINES, bool REAL_IN, bool LAP, bool GAM, class LT, c
 __device__ __forceinline__ void sourcep_body(const Src &src, LT *lds, double2 *twl)
 {
     constexpr int TPL = N / E, H = N / 2;
-    const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
+    const int tid = threadIdx.x, l = tid / TPL;
+    int t = tid % TPL;
     copy_twiddles<N, E, LINES>(src.args(0).tw, twl);
     const int ntiles = src.ntiles();
     int tile = blockIdx.x;
@@ -1717,6 +1734,7 @@ __device__ __forceinline__ void sourcep_body(const Src &src, LT *lds, double2 *t
     if constexpr (LAP) em_fetch_field<N, E>(src.args(tile).bet, pair, t, true, b0, b1);
     __builtin_amdgcn_s_waitcnt(0);
     for (;;) {
+        if constexpr (E == 8) hide(t);
         const EmArgs &a = src.args(tile);
         const int nxt = tile + gridDim.x;
         const bool more = nxt < ntiles;
@@ -1794,7 +1812,8 @@ template <int N, int E, int LINES, bool STORE_PSI, class LT, class Src, bool BOH
 __device__ __forceinline__ void densityp_body(const Src &src, LT *lds, double2 *twl, double *sh)
 {
     constexpr int TPL = N / E, NT = LINES * TPL, H = N / 2;
-    const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
+    const int tid = threadIdx.x, l = tid / TPL;
+    int t = tid % TPL;
     copy_twiddles<N, E, LINES>(src.args(0).tw, twl);
     const int ntiles = src.ntiles();
     int tile = blockIdx.x;
@@ -1810,6 +1829,7 @@ __device__ __forceinline__ void densityp_body(const Src &src, LT *lds, double2 *
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = from_f2(p0[e]);
     for (;;) {
+        if constexpr (E == 8) hide(t);
         const EmArgs &a = src.args(tile);
         const int loc = src.local(tile);
         const int nxt = tile + gridDim.x;
@@ -1954,9 +1974,25 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_lm(LmArgs a)
     lm_tile<N, E, LINES, MODE>(a, blockIdx.x, lds, sh);
 }
 
+// Waves per SIMD the persistent passes are held to.  x passes at 8 points per
+// thread: three (the density pass at 256^3 takes 57 us at 168 registers and 60
+// at the 176 it would use); 1024-point rows need 24 spills for that, and two
+// are faster (180 against 215 us on 64 x 512 x 1024).  Strided passes at 16
+// points per thread: four without a multiplier, three with one, up to
+// 256-point lines (beyond, the same bounds spill: 368 us instead of 222 for
+// the y transform of 512^3).
+template <int N, int E> constexpr int em_waves()
+{
+    return E == 8 ? (N == 1024 ? 1 : 3) : E == 16 && N <= 256 ? 2 : 1;
+}
+template <int N, int E, int MODE> constexpr int lm_waves()
+{
+    return E != 16 || N > 256 ? 1 : MODE == LM_FWD || MODE == LM_INV ? 4 : 3;
+}
+
 // Pipelined EM passes (persistent grid); LT: complex64 or complex128 LDS slots.
 template <int N, int E, int LINES, bool REAL_IN, class LT = float2>
-__global__ __launch_bounds__(LINES *(N / E)) void k_phasep(EmArgs a)
+__global__ __launch_bounds__(LINES *(N / E), (em_waves<N, E>())) void k_phasep(EmArgs a)
 {
     __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double2 twl[N];
@@ -1993,7 +2029,7 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_phasep_local(EmArgs a)
     phasep_local_body<N, E, LINES, REAL_IN, BOHM, VEXT, float2>(src, lds, twl, sct, stash);
 }
 template <int N, int E, int LINES, bool STORE_PSI, class LT = float2>
-__global__ __launch_bounds__(LINES *(N / E)) void k_densityp(EmArgs a)
+__global__ __launch_bounds__(LINES *(N / E), (em_waves<N, E>())) void k_densityp(EmArgs a)
 {
     __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double2 twl[N];
@@ -2003,7 +2039,7 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_densityp(EmArgs a)
 }
 // Pipelined LM pass (persistent grid); LT: complex64 or complex128 LDS slots.
 template <int N, int E, int LINES, int MODE, class LT>
-__global__ __launch_bounds__(LINES *(N / E)) void k_lmp(LmArgs a)
+__global__ __launch_bounds__(LINES *(N / E), (lm_waves<N, E, MODE>())) void k_lmp(LmArgs a)
 {
     using B = LmpLds<N, E, LINES, MODE, LT>;
     __shared__ LT lds[LmTile<N, E, LINES>::LDS];
@@ -2016,18 +2052,39 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_lmp(LmArgs a)
                                                                    B::TB ? kpl : a.kinp, B::TB ? k2l : a.k2_p, sh);
 }
 
-// Two-butterfly persistent LM pass (16 points per thread, 8-point plan): up
-// to four waves per SIMD, so two 512-thread blocks share a CU.
+// Two-butterfly persistent LM pass (16 points per thread, 8-point plan): four
+// waves per SIMD, as two 512-thread blocks or one of 1024.  The mode's
+// per-axis table is in LDS while it fits there beside the tile and the
+// twiddles (up to 1024-point lines).
+template <int N, int LINES, int MODE> struct Lmp2Lds {
+    static constexpr long BASE = 8L * LINES * N + 16L * R8<N>::TWN + 8L * (LINES * (N / 16) / 64 + 1);
+    static constexpr long TAB = MODE == LM_KIN ? 16L * N : MODE == LM_KERN ? 8L * N : 0;
+    static constexpr bool TB = BASE + TAB <= 160L * 1024;
+};
 template <int N, int LINES, int MODE>
 __global__ __launch_bounds__(LINES *(N / 16), 4) void k_lmp2(LmArgs a)
 {
+    using B = Lmp2Lds<N, LINES, MODE>;
     __shared__ float2 lds[LmTile<N, 16, LINES>::LDS];
     __shared__ double2 twl[R8<N>::TWN];
-    __shared__ double2 kpl[MODE == LM_KIN ? N : 1];
-    __shared__ double k2l[MODE == LM_KERN ? N : 1];
+    __shared__ double2 kpl[MODE == LM_KIN && B::TB ? N : 1];
+    __shared__ double k2l[MODE == LM_KERN && B::TB ? N : 1];
     __shared__ double sh[LmTile<N, 16, LINES>::NT / 64 + 1];
     const auto src = lm_order<LINES>(Src1<LmArgs>{a, a.s0.ntiles + a.s1.ntiles});
-    lmp2_body<N, LINES, MODE>(src, lds, twl, kpl, k2l, sh);
+    lmp2_body<N, LINES, MODE, decltype(src), B::TB>(src, lds, twl, B::TB ? kpl : a.kinp, B::TB ? k2l : a.k2_p, sh);
+}
+template <int N, int LINES, int MODE>
+__global__ __launch_bounds__(LINES *(N / 16), 4) void k_lmp2_g(const LmArgs *__restrict__ args, int tpi, int count)
+{
+    using B = Lmp2Lds<N, LINES, MODE>;
+    __shared__ float2 lds[LmTile<N, 16, LINES>::LDS];
+    __shared__ double2 twl[R8<N>::TWN];
+    __shared__ double2 kpl[MODE == LM_KIN && B::TB ? N : 1];
+    __shared__ double k2l[MODE == LM_KERN && B::TB ? N : 1];
+    __shared__ double sh[LmTile<N, 16, LINES>::NT / 64 + 1];
+    const auto src = lm_order<LINES>(SrcG<LmArgs>{args, tpi, count});
+    const LmArgs &a0 = src.args(0);
+    lmp2_body<N, LINES, MODE, decltype(src), B::TB>(src, lds, twl, B::TB ? kpl : a0.kinp, B::TB ? k2l : a0.k2_p, sh);
 }
 
 template <int N, int E, int LINES, int S>
@@ -2065,7 +2122,7 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_lm_g(const LmArgs *__restric
 // Grouped persistent prefetching passes: blocks walk the tiles of every
 // instance of the group (instance-major numbering, tpi tiles per instance).
 template <int N, int E, int LINES, int MODE>
-__global__ __launch_bounds__(LINES *(N / E)) void k_lmp_g(const LmArgs *__restrict__ args, int tpi, int count)
+__global__ __launch_bounds__(LINES *(N / E), (lm_waves<N, E, MODE>())) void k_lmp_g(const LmArgs *__restrict__ args, int tpi, int count)
 {
     using B = LmpLds<N, E, LINES, MODE, float2>;
     __shared__ float2 lds[LmTile<N, E, LINES>::LDS];
@@ -2079,7 +2136,7 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_lmp_g(const LmArgs *__restri
                                                                       B::TB ? kpl : a0.kinp, B::TB ? k2l : a0.k2_p, sh);
 }
 template <int N, int E, int LINES, bool STORE_PSI>
-__global__ __launch_bounds__(LINES *(N / E)) void k_densityp_g(const EmArgs *__restrict__ args, int tpi, int count)
+__global__ __launch_bounds__(LINES *(N / E), (em_waves<N, E>())) void k_densityp_g(const EmArgs *__restrict__ args, int tpi, int count)
 {
     __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
     __shared__ double2 twl[N];
@@ -2088,7 +2145,7 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_densityp_g(const EmArgs *__r
     densityp_body<N, E, LINES, STORE_PSI, float2>(src, lds, twl, sh);
 }
 template <int N, int E, int LINES, bool REAL_IN>
-__global__ __launch_bounds__(LINES *(N / E)) void k_phasep_g(const EmArgs *__restrict__ args, int tpi, int count)
+__global__ __launch_bounds__(LINES *(N / E), (em_waves<N, E>())) void k_phasep_g(const EmArgs *__restrict__ args, int tpi, int count)
 {
     __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
     __shared__ double2 twl[N];

@@ -57,14 +57,10 @@ __device__ __forceinline__ void sm_stages(dc (&v)[NB][E], int t, const Lay &lay,
         for (int m = 0; m < B; ++m) {
             const int j = t + TPL * m;
             dc w[R];   // shared by the NB lines
+            const Twiddles<N / (NS * R), S> tws{tw, j & (NS - 1)};
             if constexpr (NS > 1) {
-                const int jm = j & (NS - 1);
-                constexpr int STEP = N / (NS * R);
 #pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    w[r] = from_d2(tw[jm * r * STEP]);
-                    if constexpr (S > 0) w[r].y = -w[r].y;
-                }
+                for (int r = 1; r < R; ++r) w[r] = tws(r);
             }
             const int base = (j / NS) * NS * R + (j & (NS - 1));
 #pragma unroll
@@ -72,11 +68,7 @@ __device__ __forceinline__ void sm_stages(dc (&v)[NB][E], int t, const Lay &lay,
                 dc a[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) a[r] = v[b][m + r * B];
-                if constexpr (NS > 1) {
-#pragma unroll
-                    for (int r = 1; r < R; ++r) a[r] = cmul(a[r], w[r]);
-                }
-                dft<R, S>(a);
+                dft<R, S, (NS > 1)>(a, [&](int r) { return w[r]; });
                 if constexpr (LAST) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) v[b][m + r * B] = a[r];
