@@ -14,6 +14,7 @@
 #include <fstream>
 #include <map>
 #include <mutex>
+#include <new>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -170,13 +171,16 @@ struct gsn_grid_ {
     int coarse_ratio;             // 0 = no coarse schedule
     double2 *kinFc[3], *kinHc[3]; // kinetic tables of the coarse step
     DevState *st_save[2];         // device copies of the state for audits
+    std::vector<char> tab;        // host copy of the workspace's tables
+    char *tab_dev;
+    HostObs *obs_dev, *obs_host;  // where read-outs land: workspace, or pinned host memory (may be null)
     int density_blocks;
     bool static_ws;               // workspace = the library's static array (gsn_create_static)
 };
 
 
 struct Layout {
-    size_t psi, scratch, half, nyq, half2, nyq2, mass_parts, epart, st, tables, total;
+    size_t psi, scratch, half, nyq, half2, nyq2, mass_parts, epart, st, obs, tables, total;
     int density_blocks, em_blocks, lm_blocks_max;
 };
 
@@ -226,6 +230,7 @@ static Layout compute_layout(int ndim, const int32_t n[], size_t esz = 8)
     size_t ep = 4ull * (size_t)L.density_blocks + (size_t)lmb + 1024;
     L.epart = off; off = align256(off + 8ull * ep);
     L.st = off; off = align256(off + sizeof(DevState));
+    L.obs = off; off = align256(off + sizeof(HostObs));
     L.tables = off;
     size_t tb = 0;
     for (int d = 0; d < ndim; ++d) tb += align256(16ull * n[d]) * 5 + align256(8ull * n[d]);
@@ -797,70 +802,85 @@ static gsn_status run_list(gsn_grid g, const std::vector<Launch> &v)
 }
 
 // ------------------------------------------------------------------ tables
-static gsn_status upload(gsn_grid g, void *dst, const void *src, size_t bytes)
+// The tables are filled in a host copy of their part of the workspace and go to
+// the device in one transfer (a 2-D grid took eleven at creation and four more
+// with its coefficients, 15-20 us of waiting each).
+template <class T> static T *host_of(gsn_grid g, T *dev) { return (T *)(g->tab.data() + ((char *)dev - g->tab_dev)); }
+
+static gsn_status upload_tables(gsn_grid g)
 {
-    HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, g->stream));
+    HIP_TRY(hipMemcpyAsync(g->tab_dev, g->tab.data(), g->tab.size(), hipMemcpyHostToDevice, g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));
     return GSN_OK;
 }
 
-static gsn_status upload_kinetic_tables(gsn_grid g, double dz, double2 *const *kf, double2 *const *kh)
+// Read-outs land in a page of pinned host memory of the grid's own, so that they
+// need no copy; where there is none (a grid in static memory, whose creation
+// allocates nothing, or the allocation is refused) they go through the workspace.
+// Allocated and freed in relaxed capture mode: another thread may be capturing.
+static HostObs *alloc_obs()
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool sw = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    HostObs *p = nullptr;
+    if (hipHostMalloc((void **)&p, sizeof(HostObs), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
+    if (sw) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return p;
+}
+static void free_obs(HostObs *p)
+{
+    if (!p) return;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool sw = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    (void)hipHostFree(p);
+    if (sw) (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
+
+static void fill_kinetic(gsn_grid g, double dz, double2 *const *kf, double2 *const *kh)
 {
     for (int d = 0; d < g->ndim; ++d) {
         const int N = g->n[d];
-        std::vector<double2> f(N), h(N);
+        double2 *f = host_of(g, kf[d]), *h = host_of(g, kh[d]);
         for (int j = 0; j < N; ++j) {
             const double k = wavenumber(j, N, g->L[d]);
             const double thf = -g->a * k * k * dz, thh = 0.5 * thf;
             f[j] = make_double2(std::cos(thf), std::sin(thf));
             h[j] = make_double2(std::cos(thh), std::sin(thh));
         }
-        gsn_status s = upload(g, kf[d], f.data(), 16ull * N);
-        if (s) return s;
-        s = upload(g, kh[d], h.data(), 16ull * N);
-        if (s) return s;
     }
-    return GSN_OK;
 }
 
 static gsn_status upload_kinetic(gsn_grid g)
 {
-    gsn_status s = upload_kinetic_tables(g, g->dz, g->kinF, g->kinH);
-    if (s || g->coarse_ratio <= 0) return s;
-    return upload_kinetic_tables(g, g->dz * g->coarse_ratio, g->kinFc, g->kinHc);
+    fill_kinetic(g, g->dz, g->kinF, g->kinH);
+    if (g->coarse_ratio > 0) fill_kinetic(g, g->dz * g->coarse_ratio, g->kinFc, g->kinHc);
+    return upload_tables(g);
 }
 
-static gsn_status upload_static_tables(gsn_grid g)
+static void fill_static_tables(gsn_grid g)
 {
     for (int d = 0; d < g->ndim; ++d) {
         const int N = g->n[d];
-        std::vector<double2> tw(N);
-        std::vector<double> k2(N);
+        double2 *tw = host_of(g, g->tw[d]);
+        double *k2 = host_of(g, g->k2[d]);
         for (int q = 0; q < N; ++q) {
             const double ang = 2.0 * M_PI * (double)q / (double)N;
             tw[q] = make_double2(std::cos(ang), -std::sin(ang));
             const double k = wavenumber(q, N, g->L[d]);
             k2[q] = k * k;
         }
-        gsn_status s = upload(g, g->tw[d], tw.data(), 16ull * N);
-        if (s) return s;
-        s = upload(g, g->k2[d], k2.data(), 8ull * N);
-        if (s) return s;
     }
-    std::vector<double2> sct(kSinCosTable);
-    fill_sincos_table(sct.data());
-    gsn_status s = upload(g, g->sct, sct.data(), 16ull * kSinCosTable);
-    if (s) return s;
-    const double zero = 0.0;
-    const double2 one = make_double2(1.0, 0.0);
-    s = upload(g, g->k2_unit, &zero, 8);
-    if (s) return s;
-    return upload(g, g->kin_unit, &one, 16);
+    fill_sincos_table(host_of(g, g->sct));
+    *host_of(g, g->k2_unit) = 0.0;
+    *host_of(g, g->kin_unit) = make_double2(1.0, 0.0);
 }
 
 // ------------------------------------------------------------------ lifecycle
-extern "C" gsn_status gsn_create_ex(gsn_grid *out, int ndim, const int32_t n[], const double L[], int storage,
-                                    void *d_workspace, size_t bytes, void *hip_stream)
+static gsn_status create_grid(gsn_grid *out, int ndim, const int32_t n[], const double L[], int storage,
+                              void *d_workspace, size_t bytes, void *hip_stream, bool static_ws)
 {
     if (!out) return fail(GSN_EINVAL, "out is NULL");
     if (storage != GSN_C64 && storage != GSN_C128) {
@@ -931,8 +951,18 @@ extern "C" gsn_status gsn_create_ex(gsn_grid *out, int ndim, const int32_t n[], 
     g->st_save[1] = (DevState *)(ws + off); off += 256;
     g->sct = (double2 *)(ws + off); off += 16 * kSinCosTable;
     g->coarse_ratio = 0;
-    g->static_ws = false;
-    if ((s = upload_static_tables(g)) || (s = upload_kinetic(g))) {
+    g->static_ws = static_ws;
+    g->tab_dev = ws + lay.tables;
+    try {
+        g->tab.assign(lay.total - lay.tables, 0);
+    } catch (const std::bad_alloc &) {
+        delete g;
+        return fail(GSN_EINVAL, "out of host memory");
+    }
+    g->obs_dev = (HostObs *)(ws + lay.obs);
+    g->obs_host = nullptr;
+    fill_static_tables(g);
+    if ((s = upload_kinetic(g))) {
         delete g;
         return s;
     }
@@ -941,9 +971,16 @@ extern "C" gsn_status gsn_create_ex(gsn_grid *out, int ndim, const int32_t n[], 
         delete g;
         return fail(GSN_EHIP, "reset kernel launch failed");
     }
+    if (!static_ws) g->obs_host = alloc_obs();
     build_schedule(g);
     *out = g;
     return GSN_OK;
+}
+
+extern "C" gsn_status gsn_create_ex(gsn_grid *out, int ndim, const int32_t n[], const double L[], int storage,
+                                    void *d_workspace, size_t bytes, void *hip_stream)
+{
+    return create_grid(out, ndim, n, L, storage, d_workspace, bytes, hip_stream, false);
 }
 
 extern "C" gsn_status gsn_create(gsn_grid *out, int ndim, const int32_t n[], const double L[],
@@ -995,8 +1032,7 @@ extern "C" gsn_status gsn_create_static(gsn_grid *out, int ndim, const int32_t n
     }
     if (w.in_use) return fail(GSN_ESTATE, "the static workspace of this device belongs to a live grid");
     gsn_grid g = nullptr;
-    if ((s = gsn_create_ex(&g, ndim, n, L, GSN_C64, w.ptr, kStaticWorkspaceBytes, hip_stream))) return s;
-    g->static_ws = true;
+    if ((s = create_grid(&g, ndim, n, L, GSN_C64, w.ptr, kStaticWorkspaceBytes, hip_stream, true))) return s;
     w.in_use = true;
     *out = g;
     return GSN_OK;
@@ -1006,6 +1042,7 @@ extern "C" gsn_status gsn_destroy(gsn_grid g)
 {
     if (!g) return fail(GSN_EINVAL, "grid is NULL");
     (void)hipStreamSynchronize(g->stream);
+    free_obs(g->obs_host);
     if (g->static_ws) {
         std::lock_guard<std::mutex> lock(g_static_mu);
         g_static_ws[g->device].in_use = false;
@@ -1230,10 +1267,32 @@ extern "C" gsn_status gsn_step(gsn_grid g, int64_t nsteps)
     return run_list(g, g->exit_);
 }
 
+// Queue the sums of the given columns (and the state) and wait for them: one
+// launch that writes to host memory and one wait, where a read of each column
+// by itself took a copy and a wait of 15-20 us apiece (an energy 172 us).
+static gsn_status read_obs(gsn_grid g, const ObsArgs &cols, HostObs *out)
+{
+    HostObs *dst = g->obs_host ? g->obs_host : g->obs_dev;
+    hipLaunchKernelGGL(k_obs, dim3(cols.ncol + 1), dim3(256), 0, g->stream, cols, g->st, dst);
+    HIP_TRY(hipGetLastError());
+    if (!g->obs_host) HIP_TRY(hipMemcpyAsync(out, dst, sizeof(HostObs), hipMemcpyDeviceToHost, g->stream));
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    if (g->obs_host) *out = *g->obs_host;
+    return GSN_OK;
+}
+
+static gsn_status check_state(const DevState &st)
+{
+    if (st.nonfinite) return fail(GSN_ENONFINITE, "the fused FP64 mass became non-finite");
+    return GSN_OK;
+}
+
 static gsn_status read_state(gsn_grid g, DevState *st)
 {
-    HIP_TRY(hipMemcpyAsync(st, g->st, sizeof(DevState), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipStreamSynchronize(g->stream));
+    HostObs o;
+    gsn_status s = read_obs(g, ObsArgs{}, &o);
+    if (s) return s;
+    *st = o.st;
     return GSN_OK;
 }
 
@@ -1244,8 +1303,7 @@ extern "C" gsn_status gsn_sync(gsn_grid g)
     DevState st;
     gsn_status s = read_state(g, &st);
     if (s) return s;
-    if (st.nonfinite) return fail(GSN_ENONFINITE, "the fused FP64 mass became non-finite");
-    return GSN_OK;
+    return check_state(st);
 }
 
 extern "C" gsn_status gsn_phase(gsn_grid g, double *theta, int64_t *steps)
@@ -1317,18 +1375,6 @@ static double cell_volume(gsn_grid g)
     return dV;
 }
 
-static gsn_status sum_device(gsn_grid g, const double *dptr, int count, int stride, int offset,
-                             double *out)
-{
-    std::vector<double> h((size_t)count * stride);
-    HIP_TRY(hipMemcpyAsync(h.data(), dptr, 8ull * count * stride, hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipStreamSynchronize(g->stream));
-    double s = 0.0;
-    for (int i = 0; i < count; ++i) s += h[(size_t)i * stride + offset];
-    *out = s;
-    return GSN_OK;
-}
-
 extern "C" gsn_status gsn_mass(gsn_grid g, double *mass)
 {
     if (!mass) return fail(GSN_EINVAL, "mass is NULL");
@@ -1343,10 +1389,16 @@ extern "C" gsn_status gsn_mass(gsn_grid g, double *mass)
         hipLaunchKernelGGL(k_mass<256>, dim3(nb), dim3(256), 0, g->stream, g->psi, g->P, g->epart);
         HIP_TRY(hipGetLastError());
     }
+    // summed here, in the order in which the batch sums its instances' partials
+    ObsArgs cols{};
+    cols.add(g->epart, nb, 1);
+    cols.raw = nb;
+    HostObs o;
+    if ((s = read_obs(g, cols, &o))) return s;
     double sum = 0.0;
-    if ((s = sum_device(g, g->epart, nb, 1, 0, &sum))) return s;
+    for (int i = 0; i < nb; ++i) sum += o.raw[i];
     *mass = sum * cell_volume(g);
-    if ((s = gsn_sync(g))) return s;
+    if ((s = check_state(o.st))) return s;
     if (!std::isfinite(*mass)) return fail(GSN_ENONFINITE, "mass is not finite");
     return GSN_OK;
 }
@@ -1370,13 +1422,13 @@ extern "C" gsn_status gsn_energy(gsn_grid g, double e[4])
     if ((s = run_list(g, g->energy_kin))) return s;
     const int nphase = (int)g->energy_rho.back().grid.x;
     const int nkin = (int)g->energy_kin.back().grid.x;
-    double rho_sum = 0.0, rho_phi = 0.0, rho2 = 0.0, k2sum = 0.0, gsum = 0.0, slap = 0.0;
-    if ((s = sum_device(g, g->mass_parts, g->density_blocks, 1, 0, &rho_sum))) return s;
-    if ((s = sum_device(g, g->epart, nphase, 4, 0, &rho_phi))) return s;
-    if ((s = sum_device(g, g->epart, nphase, 4, 1, &rho2))) return s;
-    if ((s = sum_device(g, g->epart, nphase, 4, 2, &gsum))) return s;
-    if ((s = sum_device(g, g->epart, nphase, 4, 3, &slap))) return s;
-    if ((s = sum_device(g, g->epart + 4 * g->max_density_blocks, nkin, 1, 0, &k2sum))) return s;
+    ObsArgs cols{};
+    cols.add(g->mass_parts, g->density_blocks, 1);
+    for (int c = 0; c < 4; ++c) cols.add(g->epart + c, nphase, 4);
+    cols.add(g->epart + 4 * g->max_density_blocks, nkin, 1);
+    HostObs o;
+    if ((s = read_obs(g, cols, &o))) return s;
+    const double rho_sum = o.v[0], rho_phi = o.v[1], rho2 = o.v[2], gsum = o.v[3], slap = o.v[4], k2sum = o.v[5];
     const double dV = cell_volume(g), P = (double)g->P, K0 = kernel_k0(g);
     const double ekin = g->a * dV / P * k2sum;
     // Kerr, pressure and static potential (-sum (c_p G + V rho)) and Bohm
@@ -1387,7 +1439,7 @@ extern "C" gsn_status gsn_energy(gsn_grid g, double e[4])
     e[1] = ekin;
     e[2] = eloc;
     e[3] = enl;
-    return gsn_sync(g);
+    return check_state(o.st);
 }
 
 // ------------------------------------------------------------------ profiling
