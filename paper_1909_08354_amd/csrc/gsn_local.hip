@@ -24,6 +24,10 @@ template <int N, int V> static LKernels make_local_kernels()
     k.source[0][1] = k_source<N, E, EL, false, true>;
     k.source[1][0] = k_source<N, E, EL, true, false>;
     k.source[1][1] = k_source<N, E, EL, true, true>;
+    if constexpr (C::LAT) {
+        k.phase = k_sm_phase<N, false, float2, true>;
+        k.phase_real = k_sm_phase<N, true, float2, true>;
+    }
     k.density_p[0] = k.density_p[1] = nullptr;
     for (int i = 0; i < 8; ++i) {
         k.phase_p[i >> 2][(i >> 1) & 1][i & 1] = nullptr;

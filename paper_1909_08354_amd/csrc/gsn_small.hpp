@@ -165,8 +165,49 @@ __device__ __forceinline__ void sm_density(const EmArgs &a, int tile, const doub
     if ((tid & 63) == 0) a.partials[tile * WAVES + (tid >> 6)] = msum;
 }
 
-// Phase pass (as phase_tile without ENERGY, phi kept in FP64).
-template <int N, int LINES, bool REAL_IN, class ST>
+// The spectrum of two real rows packed as one complex line (as load_real_pair),
+// loaded raw and put together after other loads have been issued.
+template <int N, int E, class ST>
+__device__ __forceinline__ void sm_load_pair(const ST *half, const ST *nyq, long long r0, int t, ST (&a0)[E],
+                                             ST (&a1)[E], ST &n0, ST &n1)
+{
+    const ST *h0 = half + r0 * (N / 2), *h1 = h0 + N / 2;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int k = t + (N / E) * e;
+        const int idx = e < E / 2 ? k : (N - k) & (N / 2 - 1);   // the Nyquist lane reads bin 0
+        a0[e] = h0[idx];
+        a1[e] = h1[idx];
+    }
+    n0 = nyq[r0];
+    n1 = nyq[r0 + 1];
+}
+template <int N, int E, class ST>
+__device__ __forceinline__ void sm_join_pair(const ST (&a0)[E], const ST (&a1)[E], const ST &n0, const ST &n1, int t,
+                                             dc (&z)[E])
+{
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        dc x0 = ld_c(a0[e]), x1 = ld_c(a1[e]);
+        if (e < E / 2) {
+            if (t + (N / E) * e == 0) { x0.y = 0.0; x1.y = 0.0; }
+        } else if (e == E / 2 && t == 0) {
+            x0 = mk(ld_c(n0).x, 0.0);
+            x1 = mk(ld_c(n1).x, 0.0);
+        } else {
+            x0 = conj(x0);
+            x1 = conj(x1);
+        }
+        z[e] = mk(x0.x - x1.y, x0.y + x1.x);
+    }
+}
+
+// Phase pass (as phase_tile without ENERGY, phi kept in FP64).  LOCAL: with the
+// local terms and the static potential, as phase_local_tile: the spectrum of
+// lap(s) and the potential's rows are loaded with everything else, ahead of the
+// first transform (a step with pressure and Bohm term against the one-tile pass:
+// 64x128 25.9 -> 24.6 us, 64x2048 55.6 -> 52.6, 64x128x64 67.6 -> 63.6).
+template <int N, int LINES, bool REAL_IN, bool LOCAL, class ST>
 __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double2 *tw,
                                          const double2 *sct, double2 *lds)
 {
@@ -178,47 +219,66 @@ __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double
     const long long r0 = act ? 2LL * pair : 0, r1 = r0 + 1;
     const double inv_n = 1.0 / N;
     ST *p0 = (ST *)a.psi + r0 * N, *p1 = p0 + N;
-    const ST *h0 = (const ST *)a.half + r0 * (N / 2), *h1 = h0 + N / 2;
-    ST a0[E], a1[E], q0[E], q1[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int k = t + TPL * e;
-        const int idx = e < E / 2 ? k : (N - k) & (N / 2 - 1);   // the Nyquist lane reads bin 0
-        a0[e] = h0[idx];
-        a1[e] = h1[idx];
-    }
-    const ST n0 = ((const ST *)a.nyq)[r0], n1 = ((const ST *)a.nyq)[r1];
+    ST a0[E], a1[E], n0, n1, b0[E], b1[E], m0, m1, q0[E], q1[E];
+    float vx[2][E];
+    sm_load_pair<N, E, ST>((const ST *)a.half, (const ST *)a.nyq, r0, t, a0, a1, n0, n1);
     sm_load_line<E, TPL>(p0, p0, 1, true, t, q0);
     sm_load_line<E, TPL>(p1, p1, 1, true, t, q1);
-    dc z[1][E], v[2][E];
+    if constexpr (LOCAL) {
+        if (a.bohm) sm_load_pair<N, E, ST>((const ST *)a.half2, (const ST *)a.nyq2, r0, t, b0, b1, m0, m1);
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        dc x0 = ld_c(a0[e]), x1 = ld_c(a1[e]);
-        if (e < E / 2) {
-            if (t + TPL * e == 0) { x0.y = 0.0; x1.y = 0.0; }
-        } else if (e == E / 2 && t == 0) {
-            x0 = mk(ld_c(n0).x, 0.0);
-            x1 = mk(ld_c(n1).x, 0.0);
-        } else {
-            x0 = conj(x0);
-            x1 = conj(x1);
+        for (int e = 0; e < E; ++e) {
+            vx[0][e] = a.vext ? a.vext[r0 * N + t + TPL * e] : 0.0f;
+            vx[1][e] = a.vext ? a.vext[r1 * N + t + TPL * e] : 0.0f;
         }
-        z[0][e] = mk(x0.x - x1.y, x0.y + x1.x);
     }
+    dc z[1][E], v[2][E];
+    sm_join_pair<N, E, ST>(a0, a1, n0, n1, t, z[0]);
     sm_fft<1, N, E, 1>(z, t, lay, lds, 0, tw);
     sm_widen<E>(q0, true, v[0]);
     sm_widen<E>(q1, true, v[1]);
     if constexpr (!REAL_IN) sm_fft<2, N, E, 1>(v, t, lay, lds, STRIDE, tw);
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
+    if constexpr (LOCAL) {
+        float lap[2][E];
+        dc y[1][E];
+        if (a.bohm) {   // uniform over the grid
+            sm_join_pair<N, E, ST>(b0, b1, m0, m1, t, y[0]);
+            sm_fft<1, N, E, 1>(y, t, lay, lds, 0, tw);
+        }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const dc ps = REAL_IN ? v[b][e] : scl(v[b][e], inv_n);
-            const double phi = (b ? z[0][e].y : z[0][e].x) * inv_n;
-            double s, c;
-            sincos_tab(fma(a.g, norm2(ps), phi) * a.dz, sct, &s, &c);
-            v[b][e] = cmul(ps, mk(c, s));
+            lap[0][e] = a.bohm ? (float)(y[0][e].x * inv_n) : 0.0f;
+            lap[1][e] = a.bohm ? (float)(y[0][e].y * inv_n) : 0.0f;
         }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            double rho[E], U[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if constexpr (!REAL_IN) v[b][e] = scl(v[b][e], inv_n);
+                rho[e] = norm2(v[b][e]);
+            }
+            local_potential<E>(a, rho, lap[b], U);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const double phi = (b ? z[0][e].y : z[0][e].x) * inv_n;
+                double s, c;
+                sincos_tab((U[e] + (double)vx[b][e] + phi) * a.dz, sct, &s, &c);
+                v[b][e] = cmul(v[b][e], mk(c, s));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const dc ps = REAL_IN ? v[b][e] : scl(v[b][e], inv_n);
+                const double phi = (b ? z[0][e].y : z[0][e].x) * inv_n;
+                double s, c;
+                sincos_tab(fma(a.g, norm2(ps), phi) * a.dz, sct, &s, &c);
+                v[b][e] = cmul(ps, mk(c, s));
+            }
+    }
     sm_fft<2, N, E, -1>(v, t, lay, lds, STRIDE, tw);
     if (act) {
 #pragma unroll
@@ -302,12 +362,12 @@ __global__ __launch_bounds__(SmCfg<N>::WLINES *SmCfg<N>::TPL) void k_sm_density(
     __shared__ double2 lds[sm_em_slots<N, LINES>()];
     sm_density<N, LINES, STORE_PSI, ST>(a, blockIdx.x, a.tw, lds);
 }
-template <int N, bool REAL_IN, class ST = float2>
+template <int N, bool REAL_IN, class ST = float2, bool LOCAL = false>
 __global__ __launch_bounds__(SmCfg<N>::WLINES *SmCfg<N>::TPL) void k_sm_phase(EmArgs a)
 {
     constexpr int LINES = SmCfg<N>::WLINES;
     __shared__ double2 lds[sm_em_slots<N, LINES>()];
-    sm_phase<N, LINES, REAL_IN, ST>(a, blockIdx.x, a.tw, a.sct, lds);
+    sm_phase<N, LINES, REAL_IN, LOCAL, ST>(a, blockIdx.x, a.tw, a.sct, lds);
 }
 // Block ntiles sums the mass partials while the others run the tiles.
 template <int N, int MODE, class ST = float2>

@@ -80,3 +80,28 @@ def test_s4_nonfinite_mass_is_reported():
     with pytest.raises(gsn.GsnError) as e:
         grid.sync()
     assert e.value.status == gsn.GSN_ENONFINITE
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n", [(8, 8), (16, 32), (64, 128), (32, 512), (8, 2048), (32, 8, 64)])
+def test_local_terms_and_static_potential(n, mode):
+    """The phase pass with every local term (logarithmic pressure, Bohm, Kerr)
+    and a static potential; psi's bar, as the terms are evaluated in FP64 from
+    spectra stored as complex64."""
+    import torch
+    print("small local", n, "mode", mode, file=sys.stderr, flush=True)
+    L = tuple(0.5 * v for v in n)
+    psi = inputs.as_oracle_input(inputs.fluid_gaussian(n, L, 25.0, 4.0, noise=1e-3, seed=8))
+    V = np.random.default_rng(4).uniform(-1.0, 1.0, n).astype(np.float32)
+    local = (-1.02, 1.0, -1.0, 1e-10)
+    g = gsn.Grid(n, L)
+    g.set_kernel(0.5, 0.3, 0.2, 0.0)
+    g.set_coefficients(0.5, -0.2, 1e-3)
+    g.set_local_terms(*local)
+    g.set_source_fields(V_ext=torch.from_numpy(V).cuda())
+    g.set_schedule(gsn.variant_names().index("s4"))
+    g.set_nonlinear_mode(mode)
+    g.set_psi(psi)
+    g.step(12)
+    ref = orc.evolve_fields(psi, L, (0.5, 0.3, 0.2, 0.0), 0.5, -0.2, 1e-3, 12, (None, None, V), local=local)
+    assert orc.rel_l2(g.get_psi(), ref) < BAR[np.complex64]
