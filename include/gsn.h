@@ -237,6 +237,7 @@ double gsn_pass_bytes_per_point(gsn_grid grid, int i);
    pass for such grids (4 points per thread up to 256-point lines, FP64
    exchanges, both rows of a pair together).  A variant changes the Stockham radix plan, the
    tile shape and the LDS footprint, never the result beyond rounding.
+   A new grid starts with variants chosen by its size and storage.
    gsn_autotune times every variant of every pass of this grid (iters launches
    each, on a scratch copy of psi: the state is not modified) and keeps the
    fastest.  If the environment variable GSN_AUTOTUNE_CACHE names a file,

@@ -878,6 +878,34 @@ static void fill_static_tables(gsn_grid g)
     *host_of(g, g->kin_unit) = make_double2(1.0, 0.0);
 }
 
+// Schedule of a grid that has not been tuned.  Measured per step over the grids
+// from 32^2 to 2048^2 and 32^3 to 512^3, plain, with local terms and with source
+// fields, against e16 in every pass:
+// - up to 2^19 points launches and their latencies bound a pass, not its
+//   throughput: s4 (64x128 35 -> 17 us, 512^2 59 -> 29, 1024x512 63 -> 45,
+//   32x256x64 60 -> 48; at 2^20 points p8 passes it, 1024^2 70 and 62 us;
+//   128x128x64 70 and 60).  The entry transform has one exchange less to
+//   wait for in s8 (64x2048 6.3 -> 6.0 us, 1024x512 5.3 -> 5.0, short lines
+//   equal); the exit stays with the density pass, whose inverse transform takes
+//   its place in a corrected step;
+// - above, p8 (512^3 5351 -> 3480 us, 512x256x256 942 -> 791, 2048^2 193 -> 133);
+//   on 256-point lines the kinetic passes have no load to hide behind a wider
+//   tile and take p16 (256^3 358 -> 336 us), and 2048-point lines in a grid of
+//   2^21 points or less have too few tiles for p8 (2048x1024 97 -> 90 us);
+// - complex128 grids above 2^19 points keep e16: their persistent passes are the
+//   one-tile passes (256^3 567 us, e8 613).
+constexpr long long kLatencyPoints = 1LL << 19;
+static int default_variant(gsn_grid g, int pass)
+{
+    enum { E16 = 0, P16 = 2, P8 = 3, S8 = 4 };
+    if (g->P <= kLatencyPoints) return pass == P_ENTRY ? S8 : kSmallVariant;
+    if (g->storage == GSN_C128) return E16;
+    const int slow = g->ndim == 3 ? g->Nz : g->Ny;
+    if ((pass == P_KINETIC || pass == P_KERNEL) && slow == 2048 && g->P <= 1LL << 21) return P16;
+    const int line = pass == P_KINETIC ? slow : pass == P_KIN_Y ? g->Ny : 0;
+    return line == 256 ? P16 : P8;
+}
+
 // ------------------------------------------------------------------ lifecycle
 static gsn_status create_grid(gsn_grid *out, int ndim, const int32_t n[], const double L[], int storage,
                               void *d_workspace, size_t bytes, void *hip_stream, bool static_ws)
@@ -910,7 +938,7 @@ static gsn_status create_grid(gsn_grid *out, int ndim, const int32_t n[], const 
     g->Nz = ndim == 3 ? n[0] : 1;
     g->P = (long long)g->Nx * g->Ny * g->Nz;
     g->stream = (hipStream_t)hip_stream;
-    for (int i = 0; i < P_COUNT; ++i) g->var[i] = 0;
+    for (int i = 0; i < P_COUNT; ++i) g->var[i] = default_variant(g, i);
     g->store_psi = 0;
     g->max_density_blocks = lay.density_blocks;
     g->a = 0.5;
