@@ -609,6 +609,8 @@ gsn_status enqueue_group(const Group &G, int64_t nsteps, hipStream_t s)
 gsn_status capture_graph(gsn_batch b, int64_t nsteps)
 {
     if (b->exec) {
+        // its last launch may still be running
+        HIP_TRY(hipStreamSynchronize(b->stream));
         HIP_TRY(hipGraphExecDestroy(b->exec));
         b->exec = nullptr;
     }
