@@ -295,6 +295,19 @@ static LmArgs lm_base(gsn_grid g, const double2 *tw, double scale)
     return a;
 }
 
+// The coefficients of K(k), with the scale of everything from rho to phi: 1/P for
+// the transforms and 1/2 for the split of two real rows' spectra, which is stored
+// without it (all powers of two, so no bit of phi depends on where they are
+// applied; the passes in between have two multiplications a point less each).
+static void set_kernel_args(gsn_grid g, LmArgs &a)
+{
+    const double s = 0.5 / (double)g->P;
+    a.cN = g->kern.c_newton * s;
+    a.cY = g->kern.c_yukawa * s;
+    a.mY2 = g->mY2;
+    a.c0 = g->kern.c_contact * s;
+}
+
 // The pipelined LM form addresses a tile with 32-bit offsets: every offset
 // inside a tile, ((LINES - 1) ls + (N - 1) es) * 8 bytes, must stay below 2^31.
 static bool lm_fits(const Seg &s, int N, int lines)
@@ -499,9 +512,10 @@ static void build_core(gsn_grid g)
             a.kin1 = kin[X];
             a.kinp = kin[Y];
             dst.push_back(lm_launch(ky->lm_kin, ky, a, P_KIN_Y));
-            LmArgs b = lm_base(g, g->tw[Z], 1.0 / (double)Nz);
+            LmArgs b = lm_base(g, g->tw[Z], 1.0);
             b.s0 = make_seg(g->psi, (long long)Ny * Nx, 1, Nx, Nx, Ny, kz->lm_lines);
             b.kinp = kin[Z];
+            b.kin_single = 1;
             dst.push_back(lm_launch(kz->lm_kin, kz, b, P_KINETIC));
         } else {
             const NKernels *ky = KY(P_KINETIC);
@@ -542,7 +556,7 @@ static void build_core(gsn_grid g)
                     e.s0 = make_seg(g->half, H, 1, (long long)Ny * H, H, Nz, ky->lm_lines);
                     e.s1 = make_seg(g->nyq, 1, Ny, 0, Nz, 1, ky->lm_lines);
                     dst.push_back(lm_launch(ky->lm_fwd, ky, e, P_Y_FWD_SRC));
-                    LmArgs f = lm_base(g, g->tw[Z], 1.0 / ((double)Ny * Nz));
+                    LmArgs f = lm_base(g, g->tw[Z], 0.5 / (double)g->P);
                     f.s0 = make_seg(g->half, (long long)Ny * H, 1, H, H, Ny, KZ(P_LAP_RHO)->lm_lines);
                     f.s0.c1l = 1;
                     f.s0.c2o = 1;
@@ -559,7 +573,7 @@ static void build_core(gsn_grid g)
                     dst.push_back(lm_launch(ky2->lm_inv, ky2, gg, P_Y_INV_SRC));
                 } else {
                     const LKernels *ly = local_kernels_for(Ny, g->var[P_LAP_RHO]);
-                    LmArgs f = lm_base(g, g->tw[Y], 1.0 / (double)Ny);
+                    LmArgs f = lm_base(g, g->tw[Y], 0.5 / (double)g->P);
                     f.s0 = make_seg(g->half, H, 1, 0, H, 1, KY(P_LAP_RHO)->lm_lines);
                     f.s0.c1l = 1;
                     f.s1 = make_seg(g->nyq, 1, 0, 0, 1, 1, KY(P_LAP_RHO)->lm_lines);
@@ -591,7 +605,7 @@ static void build_core(gsn_grid g)
                 e.k0_dz_over_P = K0 * g->dz / (double)g->P;
             }
             dst.push_back(lm_launch(ky->lm_fwd, ky, e, P_Y_FWD_RHO));
-            LmArgs f = lm_base(g, g->tw[Z], 1.0 / ((double)Ny * Nz));
+            LmArgs f = lm_base(g, g->tw[Z], 1.0);
             f.s0 = make_seg(g->half, (long long)Ny * H, 1, H, H, Ny, kz->lm_lines);
             f.s0.c1l = 1;   // kx = line
             f.s0.c2o = 1;   // ky = outer
@@ -601,10 +615,7 @@ static void build_core(gsn_grid g)
             f.k2_1 = g->k2[X];
             f.k2_2 = g->k2[Y];
             f.k2_p = g->k2[Z];
-            f.cN = g->kern.c_newton;
-            f.cY = g->kern.c_yukawa;
-            f.mY2 = g->mY2;
-            f.c0 = g->kern.c_contact;
+            set_kernel_args(g, f);
             dst.push_back(lm_launch(kz->lm_kern, kz, f, P_KERNEL));
             LmArgs gg = lm_base(g, g->tw[Y], 1.0);
             gg.s0 = make_seg(g->half, H, 1, (long long)Ny * H, H, Nz, ky2->lm_lines);
@@ -612,17 +623,14 @@ static void build_core(gsn_grid g)
             dst.push_back(lm_launch(ky2->lm_inv, ky2, gg, P_Y_INV_PHI));
         } else {
             const NKernels *ky = KY(P_KERNEL);
-            LmArgs f = lm_base(g, g->tw[Y], 1.0 / (double)Ny);
+            LmArgs f = lm_base(g, g->tw[Y], 1.0);
             f.s0 = make_seg(g->half, H, 1, 0, H, 1, ky->lm_lines);
             f.s0.c1l = 1;
             f.s1 = make_seg(g->nyq, 1, 0, 0, 1, 1, ky->lm_lines);
             f.s1.c1f = H;
             f.k2_1 = g->k2[X];
             f.k2_p = g->k2[Y];
-            f.cN = g->kern.c_newton;
-            f.cY = g->kern.c_yukawa;
-            f.mY2 = g->mY2;
-            f.c0 = g->kern.c_contact;
+            set_kernel_args(g, f);
             if (!energy) {
                 f.reduce = 1;
                 f.mass_parts = g->mass_parts;
@@ -640,7 +648,7 @@ static void build_core(gsn_grid g)
                 e.s0 = make_seg(g->half2, H, 1, (long long)Ny * H, H, Nz, ky->lm_lines);
                 e.s1 = make_seg(g->nyq2, 1, Ny, 0, Nz, 1, ky->lm_lines);
                 dst.push_back(lm_launch(ky->lm_fwd, ky, e, P_Y_FWD_SQRT));
-                LmArgs f = lm_base(g, g->tw[Z], 1.0 / ((double)Ny * Nz));
+                LmArgs f = lm_base(g, g->tw[Z], 0.5 / (double)g->P);
                 f.s0 = make_seg(g->half2, (long long)Ny * H, 1, H, H, Ny, KZ(P_LAPLACIAN)->lm_lines);
                 f.s0.c1l = 1;
                 f.s0.c2o = 1;
@@ -657,7 +665,7 @@ static void build_core(gsn_grid g)
                 dst.push_back(lm_launch(ky2->lm_inv, ky2, gg, P_Y_INV_LAP));
             } else {
                 const LKernels *ly = local_kernels_for(Ny, g->var[P_LAPLACIAN]);
-                LmArgs f = lm_base(g, g->tw[Y], 1.0 / (double)Ny);
+                LmArgs f = lm_base(g, g->tw[Y], 0.5 / (double)g->P);
                 f.s0 = make_seg(g->half2, H, 1, 0, H, 1, KY(P_LAPLACIAN)->lm_lines);
                 f.s0.c1l = 1;
                 f.s1 = make_seg(g->nyq2, 1, 0, 0, 1, 1, KY(P_LAPLACIAN)->lm_lines);
@@ -844,11 +852,13 @@ static void fill_kinetic(gsn_grid g, double dz, double2 *const *kf, double2 *con
     for (int d = 0; d < g->ndim; ++d) {
         const int N = g->n[d];
         double2 *f = host_of(g, kf[d]), *h = host_of(g, kh[d]);
+        // the z pass has no other factor: its table holds the scale as well
+        const double s = g->ndim == 3 && d == 0 ? 1.0 / N : 1.0;
         for (int j = 0; j < N; ++j) {
             const double k = wavenumber(j, N, g->L[d]);
             const double thf = -g->a * k * k * dz, thh = 0.5 * thf;
-            f[j] = make_double2(std::cos(thf), std::sin(thf));
-            h[j] = make_double2(std::cos(thh), std::sin(thh));
+            f[j] = make_double2(s * std::cos(thf), s * std::sin(thf));
+            h[j] = make_double2(s * std::cos(thh), s * std::sin(thh));
         }
     }
 }

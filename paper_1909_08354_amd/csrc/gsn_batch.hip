@@ -487,17 +487,19 @@ LmArgs lm_args(gsn_batch b, const Instance &I, int kind, int lpt, int var_densit
         a.kin1 = kind == B_KIN_HALF ? I.kinH_x : I.kinF_x;
         a.kinp = kind == B_KIN_HALF ? I.kinH_y : I.kinF_y;
     } else {   // B_KERNEL
-        a.scale = 1.0 / I.ny;
+        // the scale from rho to phi, with the split's 1/2 (as for one grid)
+        const double sk = 0.5 / (double)I.P;
+        a.scale = 1.0;
         a.s0 = seg_of(I.half, H, 1, 0, H, 1, lpt);
         a.s0.c1l = 1;
         a.s1 = seg_of(I.nyq, 1, 0, 0, 1, 1, lpt);
         a.s1.c1f = H;
         a.k2_1 = I.k2_x;
         a.k2_p = I.k2_y;
-        a.cN = I.kern.c_newton;
-        a.cY = I.kern.c_yukawa;
+        a.cN = I.kern.c_newton * sk;
+        a.cY = I.kern.c_yukawa * sk;
         a.mY2 = I.kern.m_yukawa * I.kern.m_yukawa;
-        a.c0 = I.kern.c_contact;
+        a.c0 = I.kern.c_contact * sk;
         a.reduce = 1;
         a.mass_parts = I.mass_parts;
         const NKernels *kx = kernels_for(I.nx, var_density);

@@ -126,7 +126,7 @@ __device__ __forceinline__ void em_fft_tile(const EmArgs &a, int tile, ST *lds)
 
 // Density pass: psi = G_x psi_x / N for two rows, rho = |psi|^2, FP64 partial
 // of sum rho, then one forward FFT of Z = rho_0 + i rho_1 and the split
-// X_0[k] = (Z[k] + conj Z[N-k]) / 2, X_1[k] = (Z[k] - conj Z[N-k]) / (2i).
+// 2 X_0[k] = Z[k] + conj Z[N-k], 2 X_1[k] = (Z[k] - conj Z[N-k]) / i.
 //
 // STORE_PSI: also write psi (real space) back over the two psi_x rows, so the
 // phase pass can skip its two inverse x transforms (+8 bytes per point).
@@ -134,9 +134,13 @@ __device__ __forceinline__ void em_fft_tile(const EmArgs &a, int tile, ST *lds)
 // REAL_IN: the rows hold psi in real space (not x-spectral); the inverse x
 // transforms are skipped (the potential readout of a state between calls).
 // Split the spectrum Z = X_0 + i X_1 of two real rows held in v (one exchange
-// through LDS, so bin k can see bin N-k) into X_0[k] = (Z[k] + conj Z[N-k]) / 2,
-// X_1[k] = (Z[k] - conj Z[N-k]) / (2i); store bins 0..N/2-1 to the half rows
-// r0, r1 and the real bin N/2 to nyq.
+// through LDS, so bin k can see bin N-k) into 2 X_0[k] = Z[k] + conj Z[N-k],
+// 2 X_1[k] = (Z[k] - conj Z[N-k]) / i; store bins 0..N/2-1 to the half rows
+// r0, r1 and the real bin N/2 to nyq.  The factor 2 is taken out by the
+// multiplier pass that follows, as are the transforms' 1/N (powers of two: the
+// same bits; the density, phase and plain strided passes are bound by FP64 issue
+// at 256^3 and lose 1 to 2 multiplications a point: x_density 48.1 -> 46.9 us,
+// x_phase 89.4 -> 87.0, and 512^3 y_fwd_rho 222 -> 216).
 template <int N, int E, class LT, class ST>
 __device__ __forceinline__ void store_real_pair(const dc (&v)[E], bool act, int t, const EmLayout<N, E> &lay,
                                                 LT *lds, ST *half, ST *nyq, long long r0, long long r1)
@@ -153,13 +157,13 @@ __device__ __forceinline__ void store_real_pair(const dc (&v)[E], bool act, int 
             const dc z = v[e];
             const dc zc = conj(lds_get(lds, lay((N - k) & (N - 1))));
             const dc s = add(z, zc), d = sub(z, zc);
-            h0[k] = st_c<ST>(scl(s, 0.5));
-            h1[k] = st_c<ST>(mk(0.5 * d.y, -0.5 * d.x));
+            h0[k] = st_c<ST>(s);
+            h1[k] = st_c<ST>(mk(d.y, -d.x));
         }
         if (t == 0) {
             const dc z = v[E / 2];   // bin N/2: both halves are real
-            nyq[r0] = st_c<ST>(mk(z.x, 0.0));
-            nyq[r1] = st_c<ST>(mk(z.y, 0.0));
+            nyq[r0] = st_c<ST>(mk(2.0 * z.x, 0.0));
+            nyq[r1] = st_c<ST>(mk(2.0 * z.y, 0.0));
         }
     }
 }
@@ -285,8 +289,8 @@ __device__ __forceinline__ void potential_tile(const EmArgs &a, int tile, float2
     if (act) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            a.phi[r0 * N + t + TPL * e] = (float)(z[e].x / N);
-            a.phi[r1 * N + t + TPL * e] = (float)(z[e].y / N);
+            a.phi[r0 * N + t + TPL * e] = (float)z[e].x;
+            a.phi[r1 * N + t + TPL * e] = (float)z[e].y;
         }
     }
 }
@@ -475,8 +479,8 @@ __device__ __forceinline__ void phase_tile(const EmArgs &a, int tile, ST *lds, d
     RT phi0[E], phi1[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        phi0[e] = (RT)(z[e].x * inv_n);
-        phi1[e] = (RT)(z[e].y * inv_n);
+        phi0[e] = (RT)z[e].x;
+        phi1[e] = (RT)z[e].y;
     }
     double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll 1
@@ -587,8 +591,8 @@ __device__ __forceinline__ void phase_local_tile(const EmArgs &a, int tile, floa
     float phi0[E], phi1[E], lap0[E], lap1[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        phi0[e] = (float)(z[e].x * inv_n);
-        phi1[e] = (float)(z[e].y * inv_n);
+        phi0[e] = (float)z[e].x;
+        phi1[e] = (float)z[e].y;
         lap0[e] = 0.0f;
         lap1[e] = 0.0f;
     }
@@ -597,8 +601,8 @@ __device__ __forceinline__ void phase_local_tile(const EmArgs &a, int tile, floa
         fft<N, E, 1>(z, t, lay, lds, a.tw);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            lap0[e] = (float)(z[e].x * inv_n);
-            lap1[e] = (float)(z[e].y * inv_n);
+            lap0[e] = (float)z[e].x;
+            lap1[e] = (float)z[e].y;
         }
     }
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
@@ -698,8 +702,8 @@ __device__ __forceinline__ void source_tile(const EmArgs &a, int tile, float2 *l
         fft<N, E, 1>(z, t, lay, lds, a.tw);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            lap0[e] = (float)(z[e].x * inv_n);
-            lap1[e] = (float)(z[e].y * inv_n);
+            lap0[e] = (float)z[e].x;
+            lap1[e] = (float)z[e].y;
         }
     }
     double s0[E];
@@ -756,10 +760,11 @@ enum LmMode { LM_FWD = 0, LM_INV = 1, LM_KIN = 2, LM_KERN = 3, LM_KIN_ENERGY = 4
 struct LmArgs {
     Seg s0, s1;              // s1 used for tiles >= s0.ntiles (ntiles 0 if absent)
     const double2 *tw;       // twiddles of the pass length
-    double scale;            // output scale (FWD / INV) or multiplier scale
+    double scale;            // output scale (FWD / INV) or multiplier scale (KIN, LAP)
     const double2 *kin1, *kin2, *kinp;   // kinetic factor tables exp(-i a k_d^2 h)
+    int kin_single;                      // the line factors are 1 and kinp holds the scale
     const double *k2_1, *k2_2, *k2_p;    // k_d^2 tables
-    double cN, cY, mY2, c0;              // kernel K(k)
+    double cN, cY, mY2, c0;              // kernel K(k), its coefficients times the scale
     double *partials;                    // per-block FP64 partials (energy)
     // fused end-of-step reduction in block 0 (after the density pass)
     const double *mass_parts;
@@ -791,8 +796,10 @@ __device__ __forceinline__ void lm_tile(const LmArgs &a, int tile_in, ST *lds, d
 
     if constexpr (MODE == LM_FWD || MODE == LM_INV) {
         fft<N, E, MODE == LM_FWD ? -1 : 1>(v, t, lay, lds, a.tw);
+        if (a.scale != 1.0) {   // uniform
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = scl(v[e], a.scale);
+            for (int e = 0; e < E; ++e) v[e] = scl(v[e], a.scale);
+        }
     } else {
         // inactive lanes (lg >= nlines) read table entry 0, never past the end
         const int c1 = act ? sg.c1f + lg * sg.c1l + o * sg.c1o : 0;
@@ -817,7 +824,7 @@ __device__ __forceinline__ void lm_tile(const LmArgs &a, int tile_in, ST *lds, d
                 r = fma(r, fma(-den, r, 1.0), r);
                 // k = 0: the uniform potential is a global phase, not part of phi
                 const double K = k2 > 0.0 ? fma(num, r, a.c0) : 0.0;
-                v[e] = scl(v[e], K * a.scale);
+                v[e] = scl(v[e], K);
             }
         } else if constexpr (MODE == LM_LAP) {
             // the Laplacian: -|k|^2 (Bohm potential)
@@ -1116,8 +1123,10 @@ __device__ __forceinline__ void lmp_body(const Src &src, LT *lds, const double2 
         }
         if constexpr (MODE == LM_FWD || MODE == LM_INV) {
             fft<N, E, MODE == LM_FWD ? -1 : 1>(v, t, lay, lds, twl);
+            if (a.scale != 1.0) {   // uniform
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = scl(v[e], a.scale);
+                for (int e = 0; e < E; ++e) v[e] = scl(v[e], a.scale);
+            }
         } else {
             fft<N, E, -1>(v, t, lay, lds, twl);
             if constexpr (MODE == LM_KIN) {
@@ -1126,17 +1135,17 @@ __device__ __forceinline__ void lmp_body(const Src &src, LT *lds, const double2 
             } else {
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    // branch-free: k = 0 divides by 1 and is then zeroed
+                    // branch-free: what k = 0 gives is replaced by 0
                     const double k2 = q12 + k2l[t + TPL * e];
                     const bool pos = k2 > 0.0;
                     const double km = k2 + a.mY2;
                     const double num = fma(a.cN, km, a.cY * k2);
-                    const double den = pos ? k2 * km : 1.0;
+                    const double den = k2 * km;
                     double r = __builtin_amdgcn_rcp(den);
                     r = fma(r, fma(-den, r, 1.0), r);
                     r = fma(r, fma(-den, r, 1.0), r);
                     const double K = pos ? fma(num, r, a.c0) : 0.0;
-                    v[e] = scl(v[e], K * a.scale);
+                    v[e] = scl(v[e], K);
                 }
             }
             fft<N, E, 1>(v, t, lay, lds, twl);
@@ -1303,23 +1312,32 @@ __device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *
                 // every other kind of instruction cross
                 if constexpr (MODE == LM_KIN) __builtin_amdgcn_sched_barrier(0x27F);
                 const int j = t + TPL * m;
+                if constexpr (MODE == LM_KIN) {
+                    // the z pass has no line factor.  (In the forms that hold the
+                    // whole line in registers the second loop costs more than
+                    // it saves: 54 us become 91 at 16 points per thread, 256^3)
+                    if (a.kin_single) {   // uniform
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const int pos = j + (N / 8) * r;
-                    if constexpr (MODE == LM_KIN) {
-                        z[r] = cmul(z[r], cmul(m12, from_d2(kpl[pos])));
+                        for (int r = 0; r < 8; ++r) z[r] = cmul(z[r], from_d2(kpl[j + (N / 8) * r]));
                     } else {
-                        // branch-free: k = 0 divides by 1 and is then zeroed
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) z[r] = cmul(z[r], cmul(m12, from_d2(kpl[j + (N / 8) * r])));
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const int pos = j + (N / 8) * r;
+                        // branch-free: what k = 0 gives is replaced by 0
                         const double k2 = q12 + k2l[pos];
                         const bool pos_k = k2 > 0.0;
                         const double km = k2 + a.mY2;
                         const double num = fma(a.cN, km, a.cY * k2);
-                        const double den = pos_k ? k2 * km : 1.0;
+                        const double den = k2 * km;
                         double rc = __builtin_amdgcn_rcp(den);
                         rc = fma(rc, fma(-den, rc, 1.0), rc);
                         rc = fma(rc, fma(-den, rc, 1.0), rc);
                         const double K = pos_k ? fma(num, rc, a.c0) : 0.0;
-                        z[r] = scl(z[r], K * a.scale);
+                        z[r] = scl(z[r], K);
                     }
                 }
                 // the inverse's first stage (radix R0, no twiddles): this
@@ -1343,9 +1361,14 @@ __device__ __forceinline__ void lmp2_body(const Src &src, float2 *lds, double2 *
         for (int m = 0; m < 2; ++m) {
             dc z[8];
             r8_in<N, SL, LAST>(u, m, t, twl, z);
+            if constexpr (MODE == LM_FWD || MODE == LM_INV) {
+                if (a.scale != 1.0) {   // uniform
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) z[r] = scl(z[r], a.scale);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                if constexpr (MODE == LM_FWD || MODE == LM_INV) z[r] = scl(z[r], a.scale);
                 buf_st2(to_f2(z[r]), w.r, w.voff, (m + 2 * r) * w.step);
             }
         }
@@ -1550,8 +1573,8 @@ __device__ __forceinline__ void phasep_body(const Src &src, LT *lds, double2 *tw
         float phi0[E], phi1[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            phi0[e] = (float)(z[e].x * inv_n);
-            phi1[e] = (float)(z[e].y * inv_n);
+            phi0[e] = (float)z[e].x;
+            phi1[e] = (float)z[e].y;
         }
         em_fetch_phi<N, E>(an, npair, t, more, fp);
 #pragma unroll
@@ -1627,8 +1650,8 @@ __device__ __forceinline__ void phasep_local_body(const Src &src, LT *lds, doubl
         float phi0[E], phi1[E], lap0[E], lap1[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            phi0[e] = (float)(z[e].x * inv_n);
-            phi1[e] = (float)(z[e].y * inv_n);
+            phi0[e] = (float)z[e].x;
+            phi1[e] = (float)z[e].y;
             lap0[e] = 0.0f;
             lap1[e] = 0.0f;
         }
@@ -1647,8 +1670,8 @@ __device__ __forceinline__ void phasep_local_body(const Src &src, LT *lds, doubl
             fft<N, E, 1>(z, t, lay, lds, twl);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                stash[(2 * E + e) * NT + tid] = (float)(z[e].x * inv_n);
-                stash[(3 * E + e) * NT + tid] = (float)(z[e].y * inv_n);
+                stash[(2 * E + e) * NT + tid] = (float)z[e].x;
+                stash[(3 * E + e) * NT + tid] = (float)z[e].y;
             }
         }
 #pragma unroll
@@ -1752,8 +1775,8 @@ __device__ __forceinline__ void sourcep_body(const Src &src, LT *lds, double2 *t
             fft<N, E, 1>(z, t, lay, lds, twl);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                lap0[e] = (float)(z[e].x * inv_n);
-                lap1[e] = (float)(z[e].y * inv_n);
+                lap0[e] = (float)z[e].x;
+                lap1[e] = (float)z[e].y;
             }
             em_fetch_raw<N, E>(an.half, an.nyq, npair, t, more, fl);
         }
@@ -1790,14 +1813,14 @@ __device__ __forceinline__ void sourcep_body(const Src &src, LT *lds, double2 *t
                 const dc zz = z[e];
                 const dc zc = conj(lds_get(lds, lay((N - k) & (N - 1))));
                 const dc sm = add(zz, zc), df = sub(zz, zc);
-                buf_st2(to_f2(scl(sm, 0.5)), rsr, vo, e * TPL * 8);
-                buf_st2(to_f2(mk(0.5 * df.y, -0.5 * df.x)), rsr, vo, H * 8 + e * TPL * 8);
+                buf_st2(to_f2(sm), rsr, vo, e * TPL * 8);
+                buf_st2(to_f2(mk(df.y, -df.x)), rsr, vo, H * 8 + e * TPL * 8);
             }
         }
         if (t == 0) {
             const dc zn = z[E / 2];
-            gst(a.nyq, 2LL * pair, make_float2((float)zn.x, 0.0f));
-            gst(a.nyq, 2LL * pair + 1, make_float2((float)zn.y, 0.0f));
+            gst(a.nyq, 2LL * pair, make_float2((float)(2.0 * zn.x), 0.0f));
+            gst(a.nyq, 2LL * pair + 1, make_float2((float)(2.0 * zn.y), 0.0f));
         }
         // the LDS slots are rewritten by the next tile's first transform
         exchange_sync<EmLayout<N, E>::WAVE_LOCAL>();
@@ -1871,14 +1894,14 @@ __device__ __forceinline__ void densityp_body(const Src &src, LT *lds, double2 *
                 const dc zz = v[e];
                 const dc zc = conj(lds_get(lds, lay((N - k) & (N - 1))));
                 const dc sm = add(zz, zc), df = sub(zz, zc);
-                buf_st2(to_f2(scl(sm, 0.5)), rs, vo, e * TPL * 8);
-                buf_st2(to_f2(mk(0.5 * df.y, -0.5 * df.x)), rs, vo, H * 8 + e * TPL * 8);
+                buf_st2(to_f2(sm), rs, vo, e * TPL * 8);
+                buf_st2(to_f2(mk(df.y, -df.x)), rs, vo, H * 8 + e * TPL * 8);
             }
         }
         if (t == 0) {
             const dc zn = v[E / 2];   // bin N/2: both halves are real
-            gst(a.nyq, 2LL * pair, make_float2((float)zn.x, 0.0f));
-            gst(a.nyq, 2LL * pair + 1, make_float2((float)zn.y, 0.0f));
+            gst(a.nyq, 2LL * pair, make_float2((float)(2.0 * zn.x), 0.0f));
+            gst(a.nyq, 2LL * pair + 1, make_float2((float)(2.0 * zn.y), 0.0f));
         }
         // the LDS slots are rewritten by the next tile's first transform
         exchange_sync<EmLayout<N, E>::WAVE_LOCAL>();
@@ -1897,13 +1920,13 @@ __device__ __forceinline__ void densityp_body(const Src &src, LT *lds, double2 *
                 const dc zz = w[e];
                 const dc zc = conj(lds_get(lds, lay((N - k) & (N - 1))));
                 const dc sm = add(zz, zc), df = sub(zz, zc);
-                buf_st2(to_f2(scl(sm, 0.5)), rs, vo, e * TPL * 8);
-                buf_st2(to_f2(mk(0.5 * df.y, -0.5 * df.x)), rs, vo, H * 8 + e * TPL * 8);
+                buf_st2(to_f2(sm), rs, vo, e * TPL * 8);
+                buf_st2(to_f2(mk(df.y, -df.x)), rs, vo, H * 8 + e * TPL * 8);
             }
             if (t == 0) {
                 const dc zn = w[E / 2];
-                gst(a.nyq2, 2LL * pair, make_float2((float)zn.x, 0.0f));
-                gst(a.nyq2, 2LL * pair + 1, make_float2((float)zn.y, 0.0f));
+                gst(a.nyq2, 2LL * pair, make_float2((float)(2.0 * zn.x), 0.0f));
+                gst(a.nyq2, 2LL * pair + 1, make_float2((float)(2.0 * zn.y), 0.0f));
             }
             exchange_sync<EmLayout<N, E>::WAVE_LOCAL>();
         }

@@ -247,8 +247,8 @@ __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            lap[0][e] = a.bohm ? (float)(y[0][e].x * inv_n) : 0.0f;
-            lap[1][e] = a.bohm ? (float)(y[0][e].y * inv_n) : 0.0f;
+            lap[0][e] = a.bohm ? (float)y[0][e].x : 0.0f;
+            lap[1][e] = a.bohm ? (float)y[0][e].y : 0.0f;
         }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -261,7 +261,7 @@ __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double
             local_potential<E>(a, rho, lap[b], U);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const double phi = (b ? z[0][e].y : z[0][e].x) * inv_n;
+                const double phi = b ? z[0][e].y : z[0][e].x;
                 double s, c;
                 sincos_tab((U[e] + (double)vx[b][e] + phi) * a.dz, sct, &s, &c);
                 v[b][e] = cmul(v[b][e], mk(c, s));
@@ -273,7 +273,7 @@ __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const dc ps = REAL_IN ? v[b][e] : scl(v[b][e], inv_n);
-                const double phi = (b ? z[0][e].y : z[0][e].x) * inv_n;
+                const double phi = b ? z[0][e].y : z[0][e].x;
                 double s, c;
                 sincos_tab(fma(a.g, norm2(ps), phi) * a.dz, sct, &s, &c);
                 v[b][e] = cmul(ps, mk(c, s));
@@ -317,8 +317,10 @@ __device__ __forceinline__ void sm_lm(const LmArgs &a, int tile, double2 *lds)
     sm_widen<E>(raw, act, v[0]);
     sm_fft<1, N, E, MODE == LM_INV ? 1 : -1>(v, t, lay, lds, 0, a.tw);
     if constexpr (MODE == LM_FWD || MODE == LM_INV) {
+        if (a.scale != 1.0) {   // uniform
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[0][e] = scl(v[0][e], a.scale);
+            for (int e = 0; e < E; ++e) v[0][e] = scl(v[0][e], a.scale);
+        }
     } else {
         if constexpr (MODE == LM_KIN) {
 #pragma unroll
@@ -326,17 +328,17 @@ __device__ __forceinline__ void sm_lm(const LmArgs &a, int tile, double2 *lds)
         } else {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                // branch-free: k = 0 divides by 1 and is then zeroed
+                // branch-free: what k = 0 gives is replaced by 0
                 const double k2 = q12 + a.k2_p[t + TPL * e];
                 const bool pos = k2 > 0.0;
                 const double km = k2 + a.mY2;
                 const double num = fma(a.cN, km, a.cY * k2);
-                const double den = pos ? k2 * km : 1.0;
+                const double den = k2 * km;
                 double r = __builtin_amdgcn_rcp(den);
                 r = fma(r, fma(-den, r, 1.0), r);
                 r = fma(r, fma(-den, r, 1.0), r);
                 const double K = pos ? fma(num, r, a.c0) : 0.0;
-                v[0][e] = scl(v[0][e], K * a.scale);
+                v[0][e] = scl(v[0][e], K);
             }
         }
         sm_fft<1, N, E, 1>(v, t, lay, lds, 0, a.tw);
