@@ -1938,22 +1938,29 @@ extern "C" gsn_status gsn_step_corrected(gsn_grid g, gsn_corrector c, int64_t nc
             HIP_TRY(hipMemcpyAsync(saved, g->psi, bytes, hipMemcpyDeviceToDevice, g->stream));
             HIP_TRY(hipMemcpyAsync(g->st_save[0], g->st, sizeof(DevState), hipMemcpyDeviceToDevice, g->stream));
         }
+        float2 *const spare = corrector_fused(c) ? corrector_spare(c) : nullptr;
+        const float2 *coarse = g->psi;   // the coarse step's state
         if (!g->pot_spec.empty()) {
             // one coarse step without its closing inverse x transform, which
-            // the readout's first pass performs while it forms the density
+            // the readout's first pass performs while it forms the density; for
+            // the fused network it leaves psi in the spare image, so that the
+            // network can write the state back where it belongs (a copy of the
+            // state less per coarse step: 512^2 5 of 90 us)
             const StepLists &C = g->coarse;
             if ((s = run_list(g, C.entry)) || (s = run_list(g, C.kin_half)) || (s = run_list(g, C.nonlin)) ||
                 (s = run_list(g, C.kin_half)))
                 return s;
             for (Launch L : g->pot_spec) {
                 if (L.em) L.ea.phi = phi;
+                if (L.pass == P_DENSITY && spare) L.ea.psi_st = spare;
                 HIP_TRY(launch(L, g->stream));
             }
+            if (spare) coarse = spare;
         } else {
             if ((s = run_lists(g, g->coarse, 1))) return s;
             if ((s = run_potential(g, phi))) return s;
         }
-        if ((s = corrector_correct_inplace(c, g->psi, phi, &g->st->theta, g->stream))) return s;
+        if ((s = corrector_correct(c, coarse, phi, g->psi, &g->st->theta, g->stream))) return s;
         if (audit) {
             // the fine solver from the same state is the reference for the corrected step
             HIP_TRY(hipMemcpyAsync(corrected, g->psi, bytes, hipMemcpyDeviceToDevice, g->stream));

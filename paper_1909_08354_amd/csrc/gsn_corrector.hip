@@ -1549,8 +1549,11 @@ extern "C" gsn_status gsn_corrector_apply(gsn_corrector c, int b, const void *ps
 }
 
 // ------------------------------------------------------------------ internal hooks for corrected stepping
-gsn_status corrector_correct_inplace(gsn_corrector c, float2 *psi, const float *phi, const double *theta,
-                                     hipStream_t s)
+bool corrector_fused(gsn_corrector c) { return tiled(c); }
+float2 *corrector_spare(gsn_corrector c) { return (float2 *)c->out; }   // 8 bytes per pixel, unused by inference
+
+gsn_status corrector_correct(gsn_corrector c, const float2 *psi, const float *phi, float2 *psi_out,
+                             const double *theta, hipStream_t s)
 {
     // the corrector runs on the caller's stream for this call only; the guard
     // puts its own stream back on every return path
@@ -1563,8 +1566,8 @@ gsn_status corrector_correct_inplace(gsn_corrector c, float2 *psi, const float *
     gsn_status st = GSN_OK;
     if (tiled(c)) {
         // the four layers fused: features from (psi, phi), the corrected
-        // state into the output buffer (other tiles still read psi for their
-        // halos), then copied back over psi
+        // state into another image (other tiles still read psi for their
+        // halos)
         HIP_TRY(hipSetDevice(c->device));
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1)
@@ -1575,20 +1578,21 @@ gsn_status corrector_correct_inplace(gsn_corrector c, float2 *psi, const float *
         int seg = std::max(1, th * tw / cus);
         while (th % seg) --seg;
         const int nseg = th / seg * tw;
-        float2 *tmp = (float2 *)c->out;   // 8 bytes per pixel, unused by inference
+        float2 *dst = psi_out == psi ? corrector_spare(c) : psi_out;
         hipLaunchKernelGGL(k_corr_fused, dim3((unsigned)std::min(nseg, cus)), dim3(kFusedThreads), 0, c->stream,
-                           (const float2 *)psi, phi, tmp, c->in_scale[0], c->in_scale[1], c->in_scale[2],
+                           psi, phi, dst, c->in_scale[0], c->in_scale[1], c->in_scale[2],
                            c->out_scale, c->wf[0], c->wf[1], c->wf[2], c->wf[3], c->bias[0], c->bias[1], c->bias[2],
                            c->bias[3], c->H, c->W, seg, nseg, theta);
         if (hipGetLastError() != hipSuccess) return fail(GSN_EHIP, "corrector inference launch failed");
-        HIP_TRY(hipMemcpyAsync(psi, tmp, 8ull * c->P, hipMemcpyDeviceToDevice, c->stream));
+        if (dst != psi_out)
+            HIP_TRY(hipMemcpyAsync(psi_out, dst, 8ull * c->P, hipMemcpyDeviceToDevice, c->stream));
     } else {
         HIP_TRY(hipSetDevice(c->device));
-        hipLaunchKernelGGL(k_pack, dim3(512), dim3(256), 0, c->stream, (const float2 *)psi, phi, c->x0, c->P,
+        hipLaunchKernelGGL(k_pack, dim3(512), dim3(256), 0, c->stream, psi, phi, c->x0, c->P,
                            c->in_scale[0], c->in_scale[1], c->in_scale[2], theta);
         st = forward(c, 1);
         if (!st) {
-            hipLaunchKernelGGL(k_apply, dim3(512), dim3(256), 0, c->stream, (const float2 *)psi, c->out, psi, c->P,
+            hipLaunchKernelGGL(k_apply, dim3(512), dim3(256), 0, c->stream, psi, c->out, psi_out, c->P,
                                c->out_scale, theta);
             if (hipGetLastError() != hipSuccess) st = fail(GSN_EHIP, "corrector apply launch failed");
         }

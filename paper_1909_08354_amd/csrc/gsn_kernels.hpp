@@ -38,6 +38,7 @@ struct DevState {
 // ---------------------------------------------------------------- EM passes
 struct EmArgs {
     float2 *psi;          // rows of N complex
+    float2 *psi_st;       // where a storing density pass puts real-space psi (null: over psi)
     float2 *half;         // rows of N/2 complex (half spectrum, bins 0..N/2-1)
     float2 *nyq;          // one complex per row (bin N/2)
     const double2 *tw;    // exp(-2 pi i q / N), q < N
@@ -184,7 +185,8 @@ __device__ __forceinline__ void density_tile(const EmArgs &a, int tile, ST *lds,
     const double rs = REAL_IN ? 1.0 : inv_n * inv_n;   // |psi|^2 scale
     dc v[E];
     double rho0[E];
-    ST *p0 = (ST *)a.psi + r0 * N, *p1 = (ST *)a.psi + r1 * N;
+    const ST *p0 = (const ST *)a.psi + r0 * N, *p1 = p0 + N;
+    ST *s0 = (ST *)(a.psi_st ? a.psi_st : a.psi) + r0 * N, *s1 = s0 + N;
     load_line<E, TPL>(p0, (const ST *)a.psi, 1, act, t, v);
     if constexpr (!REAL_IN) fft<N, E, 1>(v, t, lay, lds, a.tw);
 #pragma unroll
@@ -192,7 +194,7 @@ __device__ __forceinline__ void density_tile(const EmArgs &a, int tile, ST *lds,
     if constexpr (STORE_PSI) {
         if (act) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) p0[t + TPL * e] = st_c<ST>(scl(v[e], inv_n));
+            for (int e = 0; e < E; ++e) s0[t + TPL * e] = st_c<ST>(scl(v[e], inv_n));
         }
     }
     load_line<E, TPL>(p1, (const ST *)a.psi, 1, act, t, v);
@@ -200,7 +202,7 @@ __device__ __forceinline__ void density_tile(const EmArgs &a, int tile, ST *lds,
     if constexpr (STORE_PSI) {
         if (act) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) p1[t + TPL * e] = st_c<ST>(scl(v[e], inv_n));
+            for (int e = 0; e < E; ++e) s1[t + TPL * e] = st_c<ST>(scl(v[e], inv_n));
         }
     }
     double msum = 0.0;
@@ -1422,11 +1424,11 @@ __device__ __forceinline__ void em_fetch_row(const EmArgs &a, int pair, int r, i
 }
 
 template <int N, int E>
-__device__ __forceinline__ void em_store_row(const EmArgs &a, int pair, int r, int t, const dc (&v)[E], double s)
+__device__ __forceinline__ void em_store_row(float2 *base, int pair, int r, int t, const dc (&v)[E], double s)
 {
     constexpr int TPL = N / E;
     const int pair0 = __builtin_amdgcn_readfirstlane(pair);
-    const __amdgpu_buffer_rsrc_t rs = buf_rsrc(a.psi + (long long)pair0 * 2 * N);
+    const __amdgpu_buffer_rsrc_t rs = buf_rsrc(base + (long long)pair0 * 2 * N);
     const unsigned vo = (unsigned)(((pair - pair0) * 2 * N + r * N + t) * 8);
 #pragma unroll
     for (int e = 0; e < E; ++e) buf_st2(to_f2(scl(v[e], s)), rs, vo, e * TPL * 8);
@@ -1599,7 +1601,7 @@ __device__ __forceinline__ void phasep_body(const Src &src, LT *lds, double2 *tw
                 v[e] = cmul(ps, mk(cs, sn));
             }
             fft<N, E, -1>(v, t, lay, lds, twl);
-            em_store_row<N, E>(a, pair, half, t, v, 1.0);
+            em_store_row<N, E>(a.psi, pair, half, t, v, 1.0);
         }
         if (!more) break;
         em_build_z<N, E>(fp, t, z);
@@ -1714,7 +1716,7 @@ __device__ __forceinline__ void phasep_local_body(const Src &src, LT *lds, doubl
                 v[e] = cmul(v[e], mk(cs, sn));
             }
             fft<N, E, -1>(v, t, lay, lds, twl);
-            em_store_row<N, E>(a, pair, half, t, v, 1.0);
+            em_store_row<N, E>(a.psi, pair, half, t, v, 1.0);
         }
         // the next tile's lap(sqrt rho) spectra and static potential, fetched
         // only now: their registers are free while the rows are worked on,
@@ -1865,12 +1867,12 @@ __device__ __forceinline__ void densityp_body(const Src &src, LT *lds, double2 *
         fft<N, E, 1>(v, t, lay, lds, twl);
 #pragma unroll
         for (int e = 0; e < E; ++e) rho0[e] = norm2(v[e]) * (inv_n * inv_n);
-        if constexpr (STORE_PSI) em_store_row<N, E>(a, pair, 0, t, v, inv_n);
+        if constexpr (STORE_PSI) em_store_row<N, E>(a.psi_st ? a.psi_st : a.psi, pair, 0, t, v, inv_n);
 #pragma unroll
         for (int e = 0; e < E; ++e) v[e] = from_f2(p1[e]);
         em_fetch_row<N, E>(an, npair, 1, t, more, p1);
         fft<N, E, 1>(v, t, lay, lds, twl);
-        if constexpr (STORE_PSI) em_store_row<N, E>(a, pair, 1, t, v, inv_n);
+        if constexpr (STORE_PSI) em_store_row<N, E>(a.psi_st ? a.psi_st : a.psi, pair, 1, t, v, inv_n);
         double msum = 0.0;
         dc w[BOHM ? E : 1];
 #pragma unroll

@@ -143,10 +143,11 @@ __device__ __forceinline__ void sm_density(const EmArgs &a, int tile, const doub
     sm_fft<2, N, E, 1>(v, t, lay, lds, STRIDE, tw);
     if constexpr (STORE_PSI) {
         if (act) {
+            ST *s0 = (ST *)(a.psi_st ? a.psi_st : a.psi) + r0 * N, *s1 = s0 + N;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                p0[t + TPL * e] = st_c<ST>(scl(v[0][e], inv_n));
-                p1[t + TPL * e] = st_c<ST>(scl(v[1][e], inv_n));
+                s0[t + TPL * e] = st_c<ST>(scl(v[0][e], inv_n));
+                s1[t + TPL * e] = st_c<ST>(scl(v[1][e], inv_n));
             }
         }
     }

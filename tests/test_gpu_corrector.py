@@ -278,3 +278,36 @@ def test_fused_inference_equals_pack_forward_apply(n):
     diff = np.abs(fused - ref).max()
     say(f"fused vs stepwise max |diff| {diff:.3e}")
     assert diff <= 1e-6 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("variant", range(6))
+@pytest.mark.parametrize("n", [(64, 128), (128, 1024)])
+def test_corrected_step_with_zero_weights_is_the_coarse_step(n, variant):
+    """The coarse step whose last pass leaves its state in the corrector's spare
+    image, in every schedule variant: with zero weights the corrected state is
+    the coarse state.  Both take the same passes but the last inverse
+    transform, so they differ by storage roundings at most: three per pass,
+    nine passes a step, errors adding in L2: 2 sqrt(3 * 9 * steps) 2^-24."""
+    L, steps = tuple(float(v) for v in n), 3
+    rng = np.random.default_rng(10)
+    cs, ws, vs = inputs.random_lumps(rng, n, L, 2, (4.0, 6.0))
+    psi0 = inputs.to_c64(inputs.lumps(n, L, cs, ws, vs))
+    corr = gsn.Corrector(*n, max_batch=1)
+    corr.set_weights(np.zeros(gsn.CORRECTOR_NPARAMS, dtype=np.float32))
+    corr.set_scales((1.0, 1.0, 0.1), 1e-4)
+    say("zero weights", n, "variant", variant)
+    out = []
+    for corrected in (False, True):
+        g = gsn.Grid(n, L)
+        g.set_kernel(1.0, 0.2, 0.3, 0.0)
+        g.set_coefficients(0.5, -0.5, 5e-3)
+        g.set_coarse_ratio(8)
+        g.set_schedule(variant)
+        g.set_psi(psi0)
+        for _ in range(steps):
+            if corrected:
+                assert g.step_corrected(corr, 1, 0, 0.0)[0] == 0
+            else:
+                g.step_coarse(1)
+        out.append(g.get_psi())
+    assert orc.rel_l2(out[1], out[0]) < 2 * np.sqrt(3 * 9 * steps) * 2.0 ** -24
