@@ -1030,28 +1030,46 @@ __global__ __launch_bounds__(512) void k_conv_bwd_w_t(const u16 *__restrict__ X,
     }
 }
 
-// Sum the per-block partials of one layer into the flat gradient (fixed order).
-__global__ void k_reduce_grad(const float *__restrict__ part, int nparts, int pstride, int cin, int cout,
-                              int cinn, int coutp, float *__restrict__ gflat)
+// Sum the per-block partials of one layer into the flat gradient (fixed order):
+// eight chains per parameter, combined as a tree.  Latency bounds it, so every
+// chain has a thread of its own and eight loads in flight, 32 parameters to a
+// block (one thread per parameter left most of the chip idle: 13.7 us a layer,
+// now 5.2).
+constexpr int kRgParams = 32;
+__global__ __launch_bounds__(8 * kRgParams) void k_reduce_grad(const float *__restrict__ part, int nparts, int pstride,
+                                                               int cin, int cout, int cinn, int coutp,
+                                                               float *__restrict__ gflat)
 {
-    const int nw = 9 * cout * cin;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nw + cout) return;
-    int src;
+    __shared__ float red[8][kRgParams];
+    const int nw = 9 * cout * cin, lane = threadIdx.x % kRgParams, k = threadIdx.x / kRgParams;
+    const int i = blockIdx.x * kRgParams + lane;
+    const bool act = i < nw + cout;
+    int src = 0;   // inactive lanes read parameter 0
     if (i < nw) {
         const int tap = i / (cout * cin), co = (i / cin) % cout, ci = i % cin;
         src = (tap * coutp + co) * cinn + ci;
-    } else {
+    } else if (act) {
         src = 9 * coutp * cinn + (i - nw);
     }
-    // 8 independent chains keep 8 loads in flight; combined in a fixed order
-    float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int b = 0;
-    for (; b + 8 <= nparts; b += 8)
+    const float *q = part + src;
+    const int nfull = nparts & ~7;
+    float s = 0.f;
+    int b = k;
+    for (; b + 56 < nfull; b += 64) {
+        float x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s8[k] += part[(long long)(b + k) * pstride + src];
-    for (; b < nparts; ++b) s8[0] += part[(long long)b * pstride + src];
-    gflat[i] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+        for (int j = 0; j < 8; ++j) x[j] = q[(long long)(b + 8 * j) * pstride];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += x[j];
+    }
+    for (; b < nfull; b += 8) s += q[(long long)b * pstride];
+    if (k == 0)
+        for (b = nfull; b < nparts; ++b) s += q[(long long)b * pstride];
+    red[k][lane] = s;
+    __syncthreads();
+    if (k == 0 && act)
+        gflat[i] = ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])) +
+                   ((red[4][lane] + red[5][lane]) + (red[6][lane] + red[7][lane]));
 }
 
 // ---------------------------------------------------------------- loss, Adam, packing
@@ -1448,7 +1466,7 @@ static gsn_status gradients(gsn_corrector c, int B, float *loss)
     else
         hipLaunchKernelGGL((k_conv_bwd_w<32, 16>), dim3(kBwBlocks), block, 0, c->stream, c->a[2], c->dz4, c->part, H, W,
                            np);
-    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 32 * 2 + 2 + 255) / 256), dim3(256), 0, c->stream, c->part,
+    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 32 * 2 + 2 + kRgParams - 1) / kRgParams), dim3(8 * kRgParams), 0, c->stream, c->part,
                        kBwBlocks, 9 * 16 * 32 + 16, 32, 2, 32, 16, c->grad + offs[3]);
     if (tl)
         hipLaunchKernelGGL(k_conv_bwd_data_t<16>, tiled_grid(c, ntl), block, 0, c->stream, c->dz4, c->wb[3], c->a[2],
@@ -1463,7 +1481,7 @@ static gsn_status gradients(gsn_corrector c, int B, float *loss)
     else
         hipLaunchKernelGGL((k_conv_bwd_w<32, 32>), dim3(kBwBlocks), block, 0, c->stream, c->a[1], c->dza, c->part, H, W,
                            np);
-    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 32 * 32 + 32 + 255) / 256), dim3(256), 0, c->stream, c->part,
+    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 32 * 32 + 32 + kRgParams - 1) / kRgParams), dim3(8 * kRgParams), 0, c->stream, c->part,
                        kBwBlocks, pstride_h, 32, 32, 32, 32, c->grad + offs[2]);
     if (tl)
         hipLaunchKernelGGL(k_conv_bwd_data_t<32>, tiled_grid(c, ntl), block, 0, c->stream, c->dza, c->wb[2], c->a[1], c->dzb,
@@ -1478,7 +1496,7 @@ static gsn_status gradients(gsn_corrector c, int B, float *loss)
     else
         hipLaunchKernelGGL((k_conv_bwd_w<32, 32>), dim3(kBwBlocks), block, 0, c->stream, c->a[0], c->dzb, c->part, H, W,
                            np);
-    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 32 * 32 + 32 + 255) / 256), dim3(256), 0, c->stream, c->part,
+    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 32 * 32 + 32 + kRgParams - 1) / kRgParams), dim3(8 * kRgParams), 0, c->stream, c->part,
                        kBwBlocks, pstride_h, 32, 32, 32, 32, c->grad + offs[1]);
     if (tl)
         hipLaunchKernelGGL(k_conv_bwd_data_t<32>, tiled_grid(c, ntl), block, 0, c->stream, c->dzb, c->wb[1], c->a[0], c->dza,
@@ -1492,7 +1510,7 @@ static gsn_status gradients(gsn_corrector c, int B, float *loss)
                            W, ntl);
     else
         hipLaunchKernelGGL((k_conv_bwd_w<4, 32>), dim3(kBwBlocks), block, 0, c->stream, c->x0, c->dza, c->part, H, W, np);
-    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 3 * 32 + 32 + 255) / 256), dim3(256), 0, c->stream, c->part,
+    hipLaunchKernelGGL(k_reduce_grad, dim3((9 * 3 * 32 + 32 + kRgParams - 1) / kRgParams), dim3(8 * kRgParams), 0, c->stream, c->part,
                        kBwBlocks, 9 * 32 * 16 + 32, 3, 32, 16, 32, c->grad + offs[0]);
     HIP_TRY(hipGetLastError());
     std::vector<double> h(nlb);
