@@ -1074,22 +1074,33 @@ __global__ __launch_bounds__(8 * kRgParams) void k_reduce_grad(const float *__re
 
 // ---------------------------------------------------------------- loss, Adam, packing
 // MSE over the two output channels; dZ4 = 2 (out - target) / count as bf16
-// (16 padded channels), per-block FP32 partial of the squared error.
+// (16 padded channels), per-block FP64 partial of the squared error.  48 bytes a
+// pixel bound it: four pixels' loads in flight and 16-byte stores, 8 images of
+// 512^2 in 22.8 us (4.4 TB/s; one pixel at a time with 2-byte stores 35.6).
 __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ out, const float *__restrict__ tgt,
                                              u16 *__restrict__ dz4, float inv_count, long long npix,
                                              double *__restrict__ part)
 {
     __shared__ double sh[5];
     double s = 0.0;
-    for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < npix; p += (long long)gridDim.x * 256) {
-        const float d0 = out[2 * p] - tgt[2 * p], d1 = out[2 * p + 1] - tgt[2 * p + 1];
+    const long long step = (long long)gridDim.x * 256;
+    const float2 *o2 = (const float2 *)out, *t2 = (const float2 *)tgt;
+    auto point = [&](long long p, float2 o, float2 t) {
+        const float d0 = o.x - t.x, d1 = o.y - t.y;
         s += (double)d0 * d0 + (double)d1 * d1;
-        u16 *o = dz4 + p * 16;
-        o[0] = f2bf(2.f * d0 * inv_count);
-        o[1] = f2bf(2.f * d1 * inv_count);
+        uint4 *z = (uint4 *)(dz4 + p * 16);
+        z[0] = make_uint4((unsigned)f2bf(2.f * d0 * inv_count) | (unsigned)f2bf(2.f * d1 * inv_count) << 16, 0, 0, 0);
+        z[1] = make_uint4(0, 0, 0, 0);
+    };
+    long long p = (long long)blockIdx.x * 256 + threadIdx.x;
+    for (; p + 3 * step < npix; p += 4 * step) {
+        float2 o[4], t[4];
 #pragma unroll
-        for (int c = 2; c < 16; ++c) o[c] = 0;
+        for (int j = 0; j < 4; ++j) { o[j] = o2[p + j * step]; t[j] = t2[p + j * step]; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) point(p + j * step, o[j], t[j]);
     }
+    for (; p < npix; p += step) point(p, o2[p], t2[p]);
     s = block_sum<256>(s, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
