@@ -140,9 +140,10 @@ __global__ __launch_bounds__(kPThreads) void k_batch_persistent(PArgs a)
                     }
                     __builtin_amdgcn_s_sleep(2);
                 }
-                // acquire within the XCD: drop this CU's L1 copies, so the
-                // tiles the counter covers are read from the shared L2
-                asm volatile("buffer_inv sc0\n\ts_waitcnt vmcnt(0)" ::: "memory");
+                // acquire: drop this CU's L1 copies, so the tiles the counter
+                // covers are read from the shared L2 (sc1; with sc0, the
+                // work-group scope, the L1 keeps its lines)
+                asm volatile("buffer_inv sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
             }
             s_item = x;
             s_stop = stop;
