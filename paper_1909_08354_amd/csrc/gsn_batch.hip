@@ -284,6 +284,11 @@ struct GLaunch {
     int tpi;
     int count;          // instances (persistent kernels walk count * tpi tiles)
     bool pipe;
+    bool operator==(const GLaunch &o) const
+    {
+        return fn == o.fn && grid.x == o.grid.x && block.x == o.block.x && args == o.args && tpi == o.tpi &&
+               count == o.count && pipe == o.pipe;   // one-dimensional launches
+    }
 };
 
 struct Group {
@@ -314,7 +319,9 @@ struct gsn_batch_ {
     int mode;   // 0 grouped launches in a graph, 1 persistent kernel
     char *ws;
     size_t ws_bytes;
-    float2 *scratch;   // readout staging, 16 * max P bytes
+    float2 *scratch;   // readout staging, 16 * max P bytes or more
+    size_t scratch_bytes;
+    char *st;          // the instances' states
     double *k2_unit;
     double2 *kin_unit;
     double2 *sct;      // sin / cos table of the persistent phase pass
@@ -341,10 +348,17 @@ const int kMaxInstances = 4096;
 
 struct BLayout {
     std::vector<size_t> inst_off;
-    size_t args_off, scratch_off, unit_off, queue_off, total;
+    size_t args_off, scratch_off, scratch_bytes, unit_off, queue_off, st_off, total;
 };
 
-// bytes of one instance's region (buffers, partials, state, tables)
+// The instances' states lie in one array, a stride apart (no two share a cache
+// line: different XCDs write them), so that one copy reads them all.
+constexpr size_t kStateStride = 256;
+static_assert(sizeof(DevState) <= kStateStride, "state stride");
+// values of the mass partials of one instance, as the read-out takes them
+constexpr int kMassParts = 256;
+
+// bytes of one instance's region (buffers, partials, tables)
 size_t instance_bytes(int ny, int nx)
 {
     const long long P = (long long)ny * nx;
@@ -358,7 +372,6 @@ size_t instance_bytes(int ny, int nx)
     b += align256(4ull * P);                 // half spectrum
     b += align256(8ull * ny);                // Nyquist column
     b += align256(8ull * db);                // mass partials
-    b += align256(sizeof(DevState));
     b += 6 * align256(16ull * std::max(nx, ny));   // twiddles and kinetic factors
     b += 2 * align256(8ull * std::max(nx, ny));    // |k|^2 tables
     return b;
@@ -377,12 +390,15 @@ gsn_status compute_blayout(int count, const int32_t *n, BLayout *L)
     L->args_off = off;
     off += align256((size_t)B_NKIND * count * std::max(sizeof(EmArgs), sizeof(LmArgs)));
     L->scratch_off = off;
-    off += align256(16ull * maxP);
+    L->scratch_bytes = align256(std::max(16ull * maxP, 8ull * kMassParts * std::min(count, 64)));
+    off += L->scratch_bytes;
     L->unit_off = off;
     off += 512 + 16 * kSinCosTable;
     L->queue_off = off;
     off += align256(256) + align256(8ull * count) + align256(4ull * (Q_NKIND * (count + kNQ) + count)) +
            align256(sizeof(PInst) * (size_t)count);
+    L->st_off = off;
+    off += kStateStride * count;
     L->total = off;
     return GSN_OK;
 }
@@ -405,16 +421,20 @@ gsn_status upload_sync(hipStream_t s, void *dst, const void *src, size_t bytes)
     return GSN_OK;
 }
 
+// An instance's tables lie one after the other (tw_x first, k2_y last): filled in
+// a host copy, uploaded in one transfer.
 gsn_status upload_instance_tables(gsn_batch b, Instance &I)
 {
     const int dims[2] = {I.nx, I.ny};
     const double Ls[2] = {I.Lx, I.Ly};
     double2 *tw[2] = {I.tw_x, I.tw_y}, *kf[2] = {I.kinF_x, I.kinF_y}, *kh[2] = {I.kinH_x, I.kinH_y};
     double *k2[2] = {I.k2_x, I.k2_y};
+    std::vector<char> host((char *)(I.k2_y + I.ny) - (char *)I.tw_x);
+    auto at = [&](void *dev) { return host.data() + ((char *)dev - (char *)I.tw_x); };
     for (int d = 0; d < 2; ++d) {
         const int N = dims[d];
-        std::vector<double2> t(N), f(N), h(N);
-        std::vector<double> q(N);
+        double2 *t = (double2 *)at(tw[d]), *f = (double2 *)at(kf[d]), *h = (double2 *)at(kh[d]);
+        double *q = (double *)at(k2[d]);
         for (int j = 0; j < N; ++j) {
             const double ang = 2.0 * M_PI * (double)j / (double)N;
             t[j] = make_double2(std::cos(ang), -std::sin(ang));
@@ -424,13 +444,8 @@ gsn_status upload_instance_tables(gsn_batch b, Instance &I)
             f[j] = make_double2(std::cos(thf), std::sin(thf));
             h[j] = make_double2(std::cos(thh), std::sin(thh));
         }
-        gsn_status s;
-        if ((s = upload_sync(b->stream, tw[d], t.data(), 16ull * N))) return s;
-        if ((s = upload_sync(b->stream, kf[d], f.data(), 16ull * N))) return s;
-        if ((s = upload_sync(b->stream, kh[d], h.data(), 16ull * N))) return s;
-        if ((s = upload_sync(b->stream, k2[d], q.data(), 8ull * N))) return s;
     }
-    return GSN_OK;
+    return upload_sync(b->stream, I.tw_x, host.data(), host.size());
 }
 
 double kernel_k0(const gsn_kernel &k)
@@ -523,55 +538,58 @@ bool same_tables(gsn_batch b, const Group &G)
     return true;
 }
 
-// Rebuild one group's launch descriptors and upload its argument arrays.
+// Rebuild one group's launch descriptors and upload its argument arrays (which lie
+// one after the other) in one transfer.  The recorded graph reads the arguments
+// from there, so it stays while the launches do.
+constexpr size_t kArgBytes = std::max(sizeof(EmArgs), sizeof(LmArgs));
 gsn_status build_group(gsn_batch b, Group &G)
 {
-    {
-        const int cnt = (int)G.members.size();
-        const bool uniform = same_tables(b, G);
-        for (int kind = 0; kind < B_NKIND; ++kind) {
-            const int fam = kFamOf[kind];
-            const bool is_lm = (kind == B_KIN_HALF || kind == B_KIN_FULL || kind == B_KERNEL);
-            const int N = is_lm ? G.ny : G.nx;
-            int var = G.var[fam];
-            if (var >= 2 && !uniform) var -= 2;   // same radix plan, one tile per block
-            const GKernels *k = gkernels_for(N, var);
-            GLaunch &L = G.launch[kind];
-            L.pipe = k->pipe && kind != B_ENTRY && kind != B_EXIT;
-            L.count = cnt;
-            if (is_lm) {
-                std::vector<LmArgs> v(cnt);
-                for (int m = 0; m < cnt; ++m)
-                    v[m] = lm_args(b, b->inst[G.members[m]], kind, k->lm_lines, G.var[F_DENSITY]);
-                gsn_status s = upload_sync(b->stream, G.args_dev[kind], v.data(), sizeof(LmArgs) * cnt);
-                if (s) return s;
-                L.tpi = v[0].s0.ntiles + v[0].s1.ntiles;
-                L.fn = kind == B_KERNEL ? k->lm_kern : k->lm_kin;
-                L.block = dim3(k->lm_threads());
-            } else {
-                std::vector<EmArgs> v(cnt);
-                for (int m = 0; m < cnt; ++m) v[m] = em_args(b, b->inst[G.members[m]], kind);
-                gsn_status s = upload_sync(b->stream, G.args_dev[kind], v.data(), sizeof(EmArgs) * cnt);
-                if (s) return s;
-                L.tpi = (v[0].nlines + k->em_lines - 1) / k->em_lines;
-                const bool st = G.store_psi != 0;
-                L.fn = kind == B_ENTRY ? k->em_fwd
-                     : kind == B_EXIT ? k->em_inv
-                     : kind == B_DENSITY ? (st ? k->density_store : k->density)
-                                         : (st ? k->phase_real : k->phase);
-                L.block = dim3(k->em_threads());
+    const int cnt = (int)G.members.size();
+    const bool uniform = same_tables(b, G);
+    std::vector<char> host(kArgBytes * cnt * B_NKIND);
+    for (int kind = 0; kind < B_NKIND; ++kind) {
+        char *slot = host.data() + ((char *)G.args_dev[kind] - (char *)G.args_dev[0]);
+        const int fam = kFamOf[kind];
+        const bool is_lm = (kind == B_KIN_HALF || kind == B_KIN_FULL || kind == B_KERNEL);
+        const int N = is_lm ? G.ny : G.nx;
+        int var = G.var[fam];
+        if (var >= 2 && !uniform) var -= 2;   // same radix plan, one tile per block
+        const GKernels *k = gkernels_for(N, var);
+        GLaunch L;
+        L.pipe = k->pipe && kind != B_ENTRY && kind != B_EXIT;
+        L.count = cnt;
+        if (is_lm) {
+            for (int m = 0; m < cnt; ++m) {
+                const LmArgs v = lm_args(b, b->inst[G.members[m]], kind, k->lm_lines, G.var[F_DENSITY]);
+                std::memcpy(slot + sizeof(LmArgs) * m, &v, sizeof(v));
+                L.tpi = v.s0.ntiles + v.s1.ntiles;   // the same for every member
             }
-            int grid = L.tpi * cnt;
-            if (L.pipe) {
-                const int pb = persistent_blocks(L.fn, (int)L.block.x);
-                if (pb > 0 && pb < grid) grid = pb;
+            L.fn = kind == B_KERNEL ? k->lm_kern : k->lm_kin;
+            L.block = dim3(k->lm_threads());
+        } else {
+            for (int m = 0; m < cnt; ++m) {
+                const EmArgs v = em_args(b, b->inst[G.members[m]], kind);
+                std::memcpy(slot + sizeof(EmArgs) * m, &v, sizeof(v));
+                L.tpi = (v.nlines + k->em_lines - 1) / k->em_lines;
             }
-            L.grid = dim3(grid);
-            L.args = G.args_dev[kind];
+            const bool st = G.store_psi != 0;
+            L.fn = kind == B_ENTRY ? k->em_fwd
+                 : kind == B_EXIT ? k->em_inv
+                 : kind == B_DENSITY ? (st ? k->density_store : k->density)
+                                     : (st ? k->phase_real : k->phase);
+            L.block = dim3(k->em_threads());
         }
+        int grid = L.tpi * cnt;
+        if (L.pipe) {
+            const int pb = persistent_blocks(L.fn, (int)L.block.x);
+            if (pb > 0 && pb < grid) grid = pb;
+        }
+        L.grid = dim3(grid);
+        L.args = G.args_dev[kind];
+        if (!(L == G.launch[kind])) b->dirty = true;
+        G.launch[kind] = L;
     }
-    b->dirty = true;
-    return GSN_OK;
+    return upload_sync(b->stream, G.args_dev[0], host.data(), host.size());
 }
 
 // Rebuild every group's launch descriptors and upload the argument arrays.
@@ -581,7 +599,6 @@ gsn_status build_batch(gsn_batch b)
         gsn_status s = build_group(b, G);
         if (s) return s;
     }
-    b->dirty = true;
     b->q_built = false;
     return GSN_OK;
 }
@@ -847,6 +864,8 @@ extern "C" gsn_status gsn_batch_create(gsn_batch *out, int count, int ndim, cons
         return fail(GSN_EHIP, "hipGetDevice failed");
     }
     b->scratch = (float2 *)(b->ws + lay.scratch_off);
+    b->scratch_bytes = lay.scratch_bytes;
+    b->st = b->ws + lay.st_off;
     b->k2_unit = (double *)(b->ws + lay.unit_off);
     b->kin_unit = (double2 *)(b->ws + lay.unit_off + 256);
     b->sct = (double2 *)(b->ws + lay.unit_off + 512);
@@ -872,7 +891,7 @@ extern "C" gsn_status gsn_batch_create(gsn_batch *out, int count, int ndim, cons
         I.half = (float2 *)p; p += align256(4ull * I.P);
         I.nyq = (float2 *)p; p += align256(8ull * I.ny);
         I.mass_parts = (double *)p; p += align256(8ull * db);
-        I.st = (DevState *)p; p += align256(sizeof(DevState));
+        I.st = (DevState *)(b->st + kStateStride * i);
         I.tw_x = (double2 *)p; p += align256(16ull * M);
         I.tw_y = (double2 *)p; p += align256(16ull * M);
         I.kinF_x = (double2 *)p; p += align256(16ull * M);
@@ -884,7 +903,7 @@ extern "C" gsn_status gsn_batch_create(gsn_batch *out, int count, int ndim, cons
         auto key = std::make_pair(I.ny, I.nx);
         if (!gidx.count(key)) {
             gidx[key] = (int)b->groups.size();
-            Group G;
+            Group G{};
             G.ny = I.ny;
             G.nx = I.nx;
             for (int f = 0; f < F_NFAM; ++f) G.var[f] = b->var[f];
@@ -896,11 +915,10 @@ extern "C" gsn_status gsn_batch_create(gsn_batch *out, int count, int ndim, cons
     // argument arrays: per group, per kind, one slot per member
     {
         char *p = b->ws + lay.args_off;
-        const size_t sz = std::max(sizeof(EmArgs), sizeof(LmArgs));
         for (Group &G : b->groups)
             for (int kind = 0; kind < B_NKIND; ++kind) {
                 G.args_dev[kind] = p;
-                p += sz * G.members.size();
+                p += kArgBytes * G.members.size();
             }
     }
     const double zero = 0.0;
@@ -988,7 +1006,10 @@ extern "C" gsn_status gsn_batch_set(gsn_batch b, int i, const gsn_kernel *k, dou
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(b->stream));
     I.set = true;
-    return build_batch(b);
+    b->q_built = false;
+    for (Group &G : b->groups)   // only its own group reads the instance
+        if (G.ny == I.ny && G.nx == I.nx) return build_group(b, G);
+    return fail(GSN_EINVAL, "instance not in any group");
 }
 
 extern "C" gsn_status gsn_batch_step(gsn_batch b, int64_t nsteps)
@@ -1044,9 +1065,11 @@ extern "C" gsn_status gsn_batch_sync(gsn_batch b)
             if (b->q_count[x] && head[x] < b->q_total[x])
                 return fail(GSN_EHIP, "persistent batch queue: an XCD's queue was not drained (no block ran there)");
     }
-    for (const Instance &I : b->inst) {
+    std::vector<char> all(kStateStride * b->count);
+    HIP_TRY(hipMemcpy(all.data(), b->st, all.size(), hipMemcpyDeviceToHost));
+    for (int i = 0; i < b->count; ++i) {
         DevState st;
-        HIP_TRY(hipMemcpy(&st, I.st, sizeof(st), hipMemcpyDeviceToHost));
+        std::memcpy(&st, all.data() + kStateStride * i, sizeof(st));
         if (st.nonfinite) return fail(GSN_ENONFINITE, "an instance's fused FP64 mass became non-finite");
     }
     return GSN_OK;
@@ -1075,17 +1098,25 @@ extern "C" gsn_status gsn_batch_mass(gsn_batch b, double *masses)
 {
     if (!b || !masses) return fail(GSN_EINVAL, "NULL argument");
     HIP_TRY(hipSetDevice(b->device));
-    for (int i = 0; i < b->count; ++i) {
-        const Instance &I = b->inst[i];
-        double *parts = (double *)b->scratch;
-        hipLaunchKernelGGL(k_mass<256>, dim3(256), dim3(256), 0, b->stream, I.psi, I.P, parts);
-        HIP_TRY(hipGetLastError());
-        std::vector<double> h(256);
-        HIP_TRY(hipMemcpyAsync(h.data(), parts, 8 * 256, hipMemcpyDeviceToHost, b->stream));
+    const int per = (int)std::min<size_t>(b->scratch_bytes / (8 * kMassParts), (size_t)b->count);
+    double *parts = (double *)b->scratch;
+    std::vector<double> h((size_t)per * kMassParts);
+    for (int i0 = 0; i0 < b->count; i0 += per) {
+        const int n = std::min(per, b->count - i0);
+        for (int j = 0; j < n; ++j) {
+            const Instance &I = b->inst[i0 + j];
+            hipLaunchKernelGGL(k_mass<256>, dim3(kMassParts), dim3(256), 0, b->stream, I.psi, I.P,
+                               parts + (size_t)j * kMassParts);
+            HIP_TRY(hipGetLastError());
+        }
+        HIP_TRY(hipMemcpyAsync(h.data(), parts, 8ull * kMassParts * n, hipMemcpyDeviceToHost, b->stream));
         HIP_TRY(hipStreamSynchronize(b->stream));
-        double sum = 0.0;
-        for (double v : h) sum += v;
-        masses[i] = sum * (I.Lx / I.nx) * (I.Ly / I.ny);
+        for (int j = 0; j < n; ++j) {
+            const Instance &I = b->inst[i0 + j];
+            double sum = 0.0;
+            for (int q = 0; q < kMassParts; ++q) sum += h[(size_t)j * kMassParts + q];
+            masses[i0 + j] = sum * (I.Lx / I.nx) * (I.Ly / I.ny);
+        }
     }
     return gsn_batch_sync(b);
 }

@@ -241,3 +241,63 @@ def test_persistent_queue_error_is_reported():
         b.set(i, d["kern"], d["a"], d["g"], d["dz"], inputs.to_c64(d["psi"]))
     b.step(3)
     b.sync()
+
+
+def test_instances_set_again_between_runs():
+    """An instance set again after a run (its group's arguments change, the
+    recorded graph stays unless the group's launches do) gives what a fresh
+    batch gives, bit for bit; instances left alone go on as if nothing had
+    happened, up to the storage roundings of their passes (three a pass, four
+    passes a step, errors adding in L2), should the group change its form."""
+    shapes = [(64, 64), (32, 128), (64, 64), (32, 128), (64, 64)]
+    inst, steps = make_instances(shapes, 31, 2e-3), 5
+
+    def batch(items):
+        b = gsn.Batch([d["n"] for d in inst], [d["L"] for d in inst])
+        for i, d in enumerate(items):
+            b.set(i, d["kern"], d["a"], d["g"], d["dz"], inputs.to_c64(d["psi"]))
+        return b
+
+    again = [dict(d) for d in inst]
+    again[1]["kern"] = (0.7, 0.2, 0.5, 0.1)                # same tables: the launches stay
+    again[2]["a"], again[2]["dz"] = 0.8, 1e-3              # its group is no longer uniform
+    b, ref, fresh = batch(inst), batch(inst), batch(again)
+    b.step(steps)
+    ref.step(steps)
+    for i in (1, 2):
+        d = again[i]
+        b.set(i, d["kern"], d["a"], d["g"], d["dz"], inputs.to_c64(d["psi"]))
+    b.step(steps)
+    ref.step(steps)
+    fresh.step(steps)
+    for i in range(len(inst)):
+        if i in (1, 2):
+            assert np.array_equal(b.get(i, np.complex64), fresh.get(i, np.complex64))
+            assert b.phase(i) == fresh.phase(i)
+        else:
+            assert orc.rel_l2(b.get(i), ref.get(i)) < 2 * np.sqrt(3 * 4 * 2 * steps) * 2.0 ** -24
+            assert b.phase(i)[1] == 2 * steps
+
+
+@pytest.mark.parametrize("count,n", [(1, (8, 8)), (70, (8, 8)), (3, (8, 2048))])
+def test_masses_and_state_of_many_or_tiny_instances(count, n):
+    """Masses in rounds of the staging buffer; a state that is not finite is
+    reported whichever instance holds it.  Mass bound: FP64 sums of n values
+    in another order, n * 2^-53 relative."""
+    rng = np.random.default_rng(2)
+    L = tuple(float(v) for v in n)
+    psi = [(rng.standard_normal(n) + 1j * rng.standard_normal(n)).astype(np.complex64) for _ in range(count)]
+    b = gsn.Batch([n] * count, [L] * count)
+    for i in range(count):
+        b.set(i, (1.0, 0.3, 0.5, 0.0), 0.5, -0.5, 1e-3, psi[i])
+    m = b.masses()
+    for i in range(count):
+        ref = np.sum(np.abs(psi[i].astype(np.complex128)) ** 2)
+        assert abs(m[i] - ref) <= (np.prod(n) + 4) * 2.0 ** -53 * ref
+    b.step(2)
+    b.sync()
+    psi[-1][1, 1] = np.nan
+    b.set(count - 1, (1.0, 0.3, 0.5, 0.0), 0.5, -0.5, 1e-3, psi[-1])
+    b.step(1)
+    with pytest.raises(gsn.GsnError):
+        b.sync()
