@@ -40,7 +40,7 @@ MODEL_BPP = 104.0
 
 # the sources of the single-grid passes (the batched and corrector files do
 # not change them)
-PASS_SOURCES = ("gsn_api.hip", "gsn_fft.hpp", "gsn_host.hpp", "gsn_kernels.hpp")
+PASS_SOURCES = ("gsn_api.hip", "gsn_fft.hpp", "gsn_host.hpp", "gsn_kernels.hpp", "gsn_small.hpp")
 
 
 # the Eq. (15) and coupling-field legs also run the kernels of gsn_local.hip,
