@@ -18,16 +18,16 @@ namespace gsn {
 
 struct dc { double x, y; };
 
-__device__ __forceinline__ dc mk(double x, double y) { dc r; r.x = x; r.y = y; return r; }
-__device__ __forceinline__ dc add(dc a, dc b) { return mk(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ dc sub(dc a, dc b) { return mk(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ dc scl(dc a, double s) { return mk(a.x * s, a.y * s); }
-__device__ __forceinline__ dc conj(dc a) { return mk(a.x, -a.y); }
-__device__ __forceinline__ dc cmul(dc a, dc b)
+__host__ __device__ __forceinline__ dc mk(double x, double y) { dc r; r.x = x; r.y = y; return r; }
+__host__ __device__ __forceinline__ dc add(dc a, dc b) { return mk(a.x + b.x, a.y + b.y); }
+__host__ __device__ __forceinline__ dc sub(dc a, dc b) { return mk(a.x - b.x, a.y - b.y); }
+__host__ __device__ __forceinline__ dc scl(dc a, double s) { return mk(a.x * s, a.y * s); }
+__host__ __device__ __forceinline__ dc conj(dc a) { return mk(a.x, -a.y); }
+__host__ __device__ __forceinline__ dc cmul(dc a, dc b)
 {
     return mk(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
-__device__ __forceinline__ double norm2(dc a) { return fma(a.x, a.x, a.y * a.y); }
+__host__ __device__ __forceinline__ double norm2(dc a) { return fma(a.x, a.x, a.y * a.y); }
 __device__ __forceinline__ dc from_f2(float2 v) { return mk((double)v.x, (double)v.y); }
 __device__ __forceinline__ float2 to_f2(dc v) { return make_float2((float)v.x, (float)v.y); }
 __device__ __forceinline__ dc from_d2(double2 v) { return mk(v.x, v.y); }
@@ -40,7 +40,7 @@ __device__ __forceinline__ dc lds_get(const float2 *p, int i) { return from_f2(p
 __device__ __forceinline__ dc lds_get(const double2 *p, int i) { return from_d2(p[i]); }
 
 // multiply by S*i (S = -1 forward, +1 inverse)
-template <int S> __device__ __forceinline__ dc mul_si(dc a)
+template <int S> __host__ __device__ __forceinline__ dc mul_si(dc a)
 {
     if constexpr (S > 0) return mk(-a.y, a.x);
     else return mk(a.y, -a.x);
@@ -51,14 +51,20 @@ constexpr double kC1 = 0.92387953251128675613;  // cos(pi/8)
 constexpr double kS1 = 0.38268343236508977173;  // sin(pi/8)
 constexpr double kR2 = 0.70710678118654752440;  // sqrt(1/2)
 
-// p + w q and p - w q in six FMAs: the difference is 2 p minus the sum.
-__device__ __forceinline__ void bfly(dc &p, dc &q, dc w)
+// p + w q and p - w q.  FULL: four FMAs each.  Otherwise the difference is 2 p
+// minus the sum, six FMAs in all, whose difference carries the sum's rounding as
+// well: 1% to 7% more error against extended precision over lines of 64 to 2048
+// points (FULL: 2% less to equal, both against a rounded product that is added and
+// subtracted).  That vanishes below a value that is rounded to complex64 at the
+// next exchange, so only transforms with complex128 slots are FULL.
+template <bool FULL> __host__ __device__ __forceinline__ void bfly(dc &p, dc &q, dc w)
 {
     const dc s = mk(fma(w.x, q.x, fma(-w.y, q.y, p.x)), fma(w.x, q.y, fma(w.y, q.x, p.y)));
-    q = mk(fma(2.0, p.x, -s.x), fma(2.0, p.y, -s.y));
+    if constexpr (FULL) q = mk(fma(-w.x, q.x, fma(w.y, q.y, p.x)), fma(-w.x, q.y, fma(-w.y, q.x, p.y)));
+    else q = mk(fma(2.0, p.x, -s.x), fma(2.0, p.y, -s.y));
     p = s;
 }
-__device__ __forceinline__ void bfly(dc &p, dc &q)
+__host__ __device__ __forceinline__ void bfly(dc &p, dc &q)
 {
     const dc s = add(p, q);
     q = sub(p, q);
@@ -66,12 +72,12 @@ __device__ __forceinline__ void bfly(dc &p, dc &q)
 }
 
 // a +- c u (real c)
-__device__ __forceinline__ dc axpy(double c, dc u, dc a) { return mk(fma(c, u.x, a.x), fma(c, u.y, a.y)); }
+__host__ __device__ __forceinline__ dc axpy(double c, dc u, dc a) { return mk(fma(c, u.x, a.x), fma(c, u.y, a.y)); }
 
 // DFT4 outputs from the first layer's sums and differences of the points 0, 2
 // (s02, d02) and 1, 3 (s13, d13)
 template <int S>
-__device__ __forceinline__ void dft4_out(dc s02, dc s13, dc d02, dc d13, dc &x0, dc &x1, dc &x2, dc &x3)
+__host__ __device__ __forceinline__ void dft4_out(dc s02, dc s13, dc d02, dc d13, dc &x0, dc &x1, dc &x2, dc &x3)
 {
     const dc r = mul_si<S>(d13);
     x0 = add(s02, s13);
@@ -82,7 +88,7 @@ __device__ __forceinline__ void dft4_out(dc s02, dc s13, dc d02, dc d13, dc &x0,
 
 // The same when the points 1 and 3 are c times those of s13 and d13
 template <int S>
-__device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d02, dc d13, dc &x0, dc &x1, dc &x2, dc &x3)
+__host__ __device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d02, dc d13, dc &x0, dc &x1, dc &x2, dc &x3)
 {
     const dc r = mul_si<S>(d13);
     x0 = axpy(c, s13, s02);
@@ -95,10 +101,11 @@ __device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d02, dc d1
 // multiplied by w(r) (r >= 1).  The FFT passes are bound by FP64 issue (a
 // 256-point kinetic pass issues for 95% of its time), so the multiplications
 // go into the additions that follow them: a twiddled first-layer pair takes
-// 10 instructions instead of 12 (6 instead of 8 for point 0), and a constant
+// 10 instructions instead of 12 (6 instead of 8 for point 0; two more each when FULL), and a constant
 // rotation is applied as c (1, tan) with c folded into the next layer's FMAs
 // (cos pi/8 or sqrt(1/2); the tangent never exceeds 1).
-template <int R, int S, bool TW, class W> __device__ __forceinline__ void dft(dc *a, const W &w)
+template <int R, int S, bool TW, bool FULL = false, class W>
+__host__ __device__ __forceinline__ void dft(dc *a, const W &w)
 {
     static_assert(R == 1 || R == 2 || R == 4 || R == 8 || R == 16, "unsupported radix");
     if constexpr (R > 1) {
@@ -106,7 +113,7 @@ template <int R, int S, bool TW, class W> __device__ __forceinline__ void dft(dc
         for (int i = 0; i < R / 2; ++i) {
             if constexpr (TW) {
                 if (i > 0) a[i] = cmul(a[i], w(i));
-                bfly(a[i], a[i + R / 2], w(i + R / 2));
+                bfly<FULL>(a[i], a[i + R / 2], w(i + R / 2));
             } else {
                 bfly(a[i], a[i + R / 2]);
             }
@@ -236,6 +243,9 @@ template <int STEP, int S> struct Twiddles {
     }
 };
 
+// Whether a transform with LT exchange slots computes to full FP64 accuracy.
+template <class LT> constexpr bool kFullFp64 = sizeof(LT) == sizeof(double2);
+
 // One Stockham stage and the recursion over the remaining stages.
 template <int N, int E, int S, int ST, class Lay, class LT>
 __device__ __forceinline__ void fft_stages(dc (&v)[E], int t, const Lay &lay, LT *lds,
@@ -254,7 +264,7 @@ __device__ __forceinline__ void fft_stages(dc (&v)[E], int t, const Lay &lay, LT
             dc a[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) a[r] = v[m + r * B];
-            dft<R, S, (NS > 1)>(a, Twiddles<N / (NS * R), S>{tw, j & (NS - 1)});
+            dft<R, S, (NS > 1), kFullFp64<LT>>(a, Twiddles<N / (NS * R), S>{tw, j & (NS - 1)});
             if constexpr (LAST) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) v[m + r * B] = a[r];

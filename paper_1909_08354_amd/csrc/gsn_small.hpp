@@ -45,7 +45,8 @@ template <int E, class ST> __device__ __forceinline__ void sm_widen(const ST (&r
 
 // NB lines transformed together (line b exchanges through lds + b stride): the
 // stages of fft_stages, with one twiddle read and one exchange for all of them.
-template <int NB, int N, int E, int S, int ST, class Lay>
+// Values stored as complex64 (ST) take the shorter butterflies.
+template <int NB, int N, int E, int S, int ST, bool FULL, class Lay>
 __device__ __forceinline__ void sm_stages(dc (&v)[NB][E], int t, const Lay &lay, double2 *lds, int stride,
                                           const double2 *__restrict__ tw)
 {
@@ -68,7 +69,7 @@ __device__ __forceinline__ void sm_stages(dc (&v)[NB][E], int t, const Lay &lay,
                 dc a[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) a[r] = v[b][m + r * B];
-                dft<R, S, (NS > 1)>(a, [&](int r) { return w[r]; });
+                dft<R, S, (NS > 1), FULL>(a, [&](int r) { return w[r]; });
                 if constexpr (LAST) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) v[b][m + r * B] = a[r];
@@ -85,15 +86,15 @@ __device__ __forceinline__ void sm_stages(dc (&v)[NB][E], int t, const Lay &lay,
 #pragma unroll
                 for (int e = 0; e < E; ++e) v[b][e] = lds_get(lds + b * stride, lay(t + TPL * e));
             exchange_sync<Lay::WAVE_LOCAL>();
-            sm_stages<NB, N, E, S, ST + 1>(v, t, lay, lds, stride, tw);
+            sm_stages<NB, N, E, S, ST + 1, FULL>(v, t, lay, lds, stride, tw);
         }
     }
 }
-template <int NB, int N, int E, int S, class Lay>
+template <int NB, int N, int E, int S, class ST, class Lay>
 __device__ __forceinline__ void sm_fft(dc (&v)[NB][E], int t, const Lay &lay, double2 *lds, int stride,
                                        const double2 *__restrict__ tw)
 {
-    sm_stages<NB, N, E, S, 0>(v, t, lay, lds, stride, tw);
+    sm_stages<NB, N, E, S, 0, kFullFp64<ST>>(v, t, lay, lds, stride, tw);
 }
 
 // slots of an x block of LINES pairs (two rows per pair)
@@ -114,7 +115,7 @@ __device__ __forceinline__ void sm_em_fft(const EmArgs &a, int tile, const doubl
     dc v[1][E];
     sm_load_line<E, TPL>(p, (const ST *)a.psi, 1, act, t, raw);
     sm_widen<E>(raw, act, v[0]);
-    sm_fft<1, N, E, S>(v, t, lay, lds, 0, tw);
+    sm_fft<1, N, E, S, ST>(v, t, lay, lds, 0, tw);
     if (act) {
 #pragma unroll
         for (int e = 0; e < E; ++e) p[t + TPL * e] = st_c<ST>(scl(v[0][e], a.scale));
@@ -140,7 +141,7 @@ __device__ __forceinline__ void sm_density(const EmArgs &a, int tile, const doub
     sm_load_line<E, TPL>(p1, (const ST *)a.psi, 1, act, t, q1);
     sm_widen<E>(q0, act, v[0]);
     sm_widen<E>(q1, act, v[1]);
-    sm_fft<2, N, E, 1>(v, t, lay, lds, STRIDE, tw);
+    sm_fft<2, N, E, 1, ST>(v, t, lay, lds, STRIDE, tw);
     if constexpr (STORE_PSI) {
         if (act) {
             ST *s0 = (ST *)(a.psi_st ? a.psi_st : a.psi) + r0 * N, *s1 = s0 + N;
@@ -159,7 +160,7 @@ __device__ __forceinline__ void sm_density(const EmArgs &a, int tile, const doub
         msum += rho0 + rho1;
         z[0][e] = mk(rho0, rho1);
     }
-    sm_fft<1, N, E, -1>(z, t, lay, lds, 0, tw);
+    sm_fft<1, N, E, -1, ST>(z, t, lay, lds, 0, tw);
     store_real_pair<N, E>(z[0], act, t, lay, lds, (ST *)a.half, (ST *)a.nyq, r0, r1);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) msum += __shfl_xor(msum, o, 64);
@@ -235,16 +236,16 @@ __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double
     }
     dc z[1][E], v[2][E];
     sm_join_pair<N, E, ST>(a0, a1, n0, n1, t, z[0]);
-    sm_fft<1, N, E, 1>(z, t, lay, lds, 0, tw);
+    sm_fft<1, N, E, 1, ST>(z, t, lay, lds, 0, tw);
     sm_widen<E>(q0, true, v[0]);
     sm_widen<E>(q1, true, v[1]);
-    if constexpr (!REAL_IN) sm_fft<2, N, E, 1>(v, t, lay, lds, STRIDE, tw);
+    if constexpr (!REAL_IN) sm_fft<2, N, E, 1, ST>(v, t, lay, lds, STRIDE, tw);
     if constexpr (LOCAL) {
         float lap[2][E];
         dc y[1][E];
         if (a.bohm) {   // uniform over the grid
             sm_join_pair<N, E, ST>(b0, b1, m0, m1, t, y[0]);
-            sm_fft<1, N, E, 1>(y, t, lay, lds, 0, tw);
+            sm_fft<1, N, E, 1, ST>(y, t, lay, lds, 0, tw);
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -280,7 +281,7 @@ __device__ __forceinline__ void sm_phase(const EmArgs &a, int tile, const double
                 v[b][e] = cmul(ps, mk(c, s));
             }
     }
-    sm_fft<2, N, E, -1>(v, t, lay, lds, STRIDE, tw);
+    sm_fft<2, N, E, -1, ST>(v, t, lay, lds, STRIDE, tw);
     if (act) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -316,7 +317,7 @@ __device__ __forceinline__ void sm_lm(const LmArgs &a, int tile, double2 *lds)
     if constexpr (MODE == LM_KIN) m12 = scl(cmul(from_d2(a.kin1[c1]), from_d2(a.kin2[c2])), a.scale);
     if constexpr (MODE == LM_KERN) q12 = a.k2_1[c1] + a.k2_2[c2];
     sm_widen<E>(raw, act, v[0]);
-    sm_fft<1, N, E, MODE == LM_INV ? 1 : -1>(v, t, lay, lds, 0, a.tw);
+    sm_fft<1, N, E, MODE == LM_INV ? 1 : -1, ST>(v, t, lay, lds, 0, a.tw);
     if constexpr (MODE == LM_FWD || MODE == LM_INV) {
         if (a.scale != 1.0) {   // uniform
 #pragma unroll
@@ -342,7 +343,7 @@ __device__ __forceinline__ void sm_lm(const LmArgs &a, int tile, double2 *lds)
                 v[0][e] = scl(v[0][e], K);
             }
         }
-        sm_fft<1, N, E, 1>(v, t, lay, lds, 0, a.tw);
+        sm_fft<1, N, E, 1, ST>(v, t, lay, lds, 0, a.tw);
     }
     if (act) {
 #pragma unroll
