@@ -51,17 +51,11 @@ constexpr double kC1 = 0.92387953251128675613;  // cos(pi/8)
 constexpr double kS1 = 0.38268343236508977173;  // sin(pi/8)
 constexpr double kR2 = 0.70710678118654752440;  // sqrt(1/2)
 
-// p + w q and p - w q.  FULL: four FMAs each.  Otherwise the difference is 2 p
-// minus the sum, six FMAs in all, whose difference carries the sum's rounding as
-// well: 1% to 7% more error against extended precision over lines of 64 to 2048
-// points (FULL: 2% less to equal, both against a rounded product that is added and
-// subtracted).  That vanishes below a value that is rounded to complex64 at the
-// next exchange, so only transforms with complex128 slots are FULL.
-template <bool FULL> __host__ __device__ __forceinline__ void bfly(dc &p, dc &q, dc w)
+// p + w q and p - w q in six FMAs: the difference is 2 p minus the sum.
+__host__ __device__ __forceinline__ void bfly(dc &p, dc &q, dc w)
 {
     const dc s = mk(fma(w.x, q.x, fma(-w.y, q.y, p.x)), fma(w.x, q.y, fma(w.y, q.x, p.y)));
-    if constexpr (FULL) q = mk(fma(-w.x, q.x, fma(w.y, q.y, p.x)), fma(-w.x, q.y, fma(-w.y, q.x, p.y)));
-    else q = mk(fma(2.0, p.x, -s.x), fma(2.0, p.y, -s.y));
+    q = mk(fma(2.0, p.x, -s.x), fma(2.0, p.y, -s.y));
     p = s;
 }
 __host__ __device__ __forceinline__ void bfly(dc &p, dc &q)
@@ -101,9 +95,16 @@ __host__ __device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d
 // multiplied by w(r) (r >= 1).  The FFT passes are bound by FP64 issue (a
 // 256-point kinetic pass issues for 95% of its time), so the multiplications
 // go into the additions that follow them: a twiddled first-layer pair takes
-// 10 instructions instead of 12 (6 instead of 8 for point 0; two more each when FULL), and a constant
+// 10 instructions instead of 12 (6 instead of 8 for point 0), and a constant
 // rotation is applied as c (1, tan) with c folded into the next layer's FMAs
 // (cos pi/8 or sqrt(1/2); the tangent never exceeds 1).
+// FULL: products with twiddles, and with cos and sin of pi/8, are rounded on their
+// own.  The short forms err by 1% to 3% more per transform (lines of 16 to 2048
+// points against extended precision), the folded pi/8 the same way in every step:
+// 12 steps of a complex128 256^2 state on the 16-point plan are 14% further off
+// (1.65e-14 against 1.45e-14; shapes with lines up to 1024 points 2% to 14%).
+// Beside values that are rounded to complex64 at the next exchange it vanishes, so
+// only complex128 values in complex128 slots are FULL.
 template <int R, int S, bool TW, bool FULL = false, class W>
 __host__ __device__ __forceinline__ void dft(dc *a, const W &w)
 {
@@ -113,7 +114,12 @@ __host__ __device__ __forceinline__ void dft(dc *a, const W &w)
         for (int i = 0; i < R / 2; ++i) {
             if constexpr (TW) {
                 if (i > 0) a[i] = cmul(a[i], w(i));
-                bfly<FULL>(a[i], a[i + R / 2], w(i + R / 2));
+                if constexpr (FULL) {
+                    a[i + R / 2] = cmul(a[i + R / 2], w(i + R / 2));
+                    bfly(a[i], a[i + R / 2]);
+                } else {
+                    bfly(a[i], a[i + R / 2], w(i + R / 2));
+                }
             } else {
                 bfly(a[i], a[i + R / 2]);
             }
@@ -145,11 +151,16 @@ __host__ __device__ __forceinline__ void dft(dc *a, const W &w)
         dft4_out<S>(y[0][0], y[1][0], y[2][0], y[3][0], a[0], a[4], a[8], a[12]);
         constexpr double t = kS1 / kC1;   // tan(pi/8)
         {   // k = 1: angles pi/8, pi/4, 3 pi/8
-            const dc v = y[1][1], u1 = mk(fma(-S * t, v.y, v.x), fma(S * t, v.x, v.y));
-            const dc u3 = mk(fma(t, y[3][1].x, -S * y[3][1].y), fma(t, y[3][1].y, S * y[3][1].x));
             const dc u2 = add(y[2][1], mul_si<S>(y[2][1]));
-            dft4_out<S>(kC1, axpy(kR2, u2, y[0][1]), add(u1, u3), axpy(-kR2, u2, y[0][1]), sub(u1, u3), a[1], a[5],
-                        a[9], a[13]);
+            const dc p = axpy(kR2, u2, y[0][1]), q = axpy(-kR2, u2, y[0][1]);
+            if constexpr (FULL) {
+                const dc z1 = cmul(y[1][1], mk(kC1, S * kS1)), z3 = cmul(y[3][1], mk(kS1, S * kC1));
+                dft4_out<S>(p, add(z1, z3), q, sub(z1, z3), a[1], a[5], a[9], a[13]);
+            } else {
+                const dc v = y[1][1], u1 = mk(fma(-S * t, v.y, v.x), fma(S * t, v.x, v.y));
+                const dc u3 = mk(fma(t, y[3][1].x, -S * y[3][1].y), fma(t, y[3][1].y, S * y[3][1].x));
+                dft4_out<S>(kC1, p, add(u1, u3), q, sub(u1, u3), a[1], a[5], a[9], a[13]);
+            }
         }
         {   // k = 2: pi/4, pi/2, 3 pi/4
             const dc u1 = add(y[1][2], mul_si<S>(y[1][2])), u3 = sub(mul_si<S>(y[3][2]), y[3][2]);
@@ -157,11 +168,16 @@ __host__ __device__ __forceinline__ void dft(dc *a, const W &w)
             dft4_out<S>(kR2, add(y[0][2], b2), add(u1, u3), sub(y[0][2], b2), sub(u1, u3), a[2], a[6], a[10], a[14]);
         }
         {   // k = 3: 3 pi/8, 3 pi/4, 9 pi/8
-            const dc u1 = mk(fma(t, y[1][3].x, -S * y[1][3].y), fma(t, y[1][3].y, S * y[1][3].x));
             const dc u2 = sub(mul_si<S>(y[2][3]), y[2][3]);
-            const dc v = y[3][3], u3 = mk(fma(S * t, v.y, -v.x), fma(-S * t, v.x, -v.y));
-            dft4_out<S>(kC1, axpy(kR2, u2, y[0][3]), add(u1, u3), axpy(-kR2, u2, y[0][3]), sub(u1, u3), a[3], a[7],
-                        a[11], a[15]);
+            const dc p = axpy(kR2, u2, y[0][3]), q = axpy(-kR2, u2, y[0][3]);
+            if constexpr (FULL) {
+                const dc z1 = cmul(y[1][3], mk(kS1, S * kC1)), z3 = cmul(y[3][3], mk(-kC1, -S * kS1));
+                dft4_out<S>(p, add(z1, z3), q, sub(z1, z3), a[3], a[7], a[11], a[15]);
+            } else {
+                const dc u1 = mk(fma(t, y[1][3].x, -S * y[1][3].y), fma(t, y[1][3].y, S * y[1][3].x));
+                const dc v = y[3][3], u3 = mk(fma(S * t, v.y, -v.x), fma(-S * t, v.x, -v.y));
+                dft4_out<S>(kC1, p, add(u1, u3), q, sub(u1, u3), a[3], a[7], a[11], a[15]);
+            }
         }
     }
 }

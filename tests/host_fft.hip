@@ -15,6 +15,7 @@ using gsn::mk;
 typedef std::complex<long double> ld;
 
 static std::vector<double2> g_tw;
+constexpr bool kFull = gsn::kFullFp64<double2>;
 
 template <int N, int E, int ST, bool PRODUCTS> static void stages(std::vector<dc> &v)
 {
@@ -29,9 +30,9 @@ template <int N, int E, int ST, bool PRODUCTS> static void stages(std::vector<dc
             for (int r = 0; r < R; ++r) a[r] = v[j + r * (N / R)];
             if constexpr (PRODUCTS) {
                 for (int r = 1; r < R; ++r) a[r] = gsn::cmul(a[r], w(r));
-                gsn::dft<R, -1, false>(a, w);
+                gsn::dft<R, -1, false, kFull>(a, w);
             } else {
-                gsn::dft<R, -1, (NS > 1), gsn::kFullFp64<double2>>(a, w);
+                gsn::dft<R, -1, (NS > 1), kFull>(a, w);
             }
             for (int r = 0; r < R; ++r) o[(j / NS) * NS * R + jm + r * NS] = a[r];
         }

@@ -1,0 +1,89 @@
+"""Rounding error of the solver against extended precision: the schedule and the
+transforms may be chosen for speed only where the error does not grow."""
+import numpy as np
+import pytest
+import scipy.fft
+
+pytestmark = pytest.mark.gpu
+
+KERN = (1.0, 0.3, 0.1, 0.0)
+DZ, STEPS = 1e-3, 12
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def evolve_ld(psi, L, g):
+    """STEPS split steps in extended precision (numpy's longdouble)."""
+    ld = np.longdouble
+    n = psi.shape
+    two_pi = 2 * ld("3.14159265358979323846264338327950288")
+    k2 = np.zeros(n, ld)
+    for ax in range(len(n)):
+        k = two_pi / ld(L[ax]) * np.fft.fftfreq(n[ax], 1.0 / n[ax]).astype(ld)
+        k2 = k2 + (k * k).reshape([-1 if d == ax else 1 for d in range(len(n))])
+    cN, cY, mY, _ = [ld(v) for v in KERN]
+    K = np.zeros(n, ld)
+    K[k2 > 0] = cN / k2[k2 > 0]
+    K += cY / (k2 + mY * mY)
+
+    def phase(t):
+        return np.cos(t) + 1j * np.sin(t)
+
+    def kinetic(p, m):
+        return scipy.fft.ifftn(scipy.fft.fftn(p, workers=8) * m, workers=8)
+
+    half, full = phase(-ld(0.25) * ld(DZ) * k2), phase(-ld(0.5) * ld(DZ) * k2)
+    psi = kinetic(psi.astype(np.clongdouble), half)
+    for i in range(STEPS):
+        rho = psi.real ** 2 + psi.imag ** 2
+        phi = scipy.fft.ifftn(K * scipy.fft.fftn(rho.astype(np.clongdouble), workers=8), workers=8).real
+        psi = kinetic(psi * phase((ld(g) * rho + phi) * ld(DZ)), full if i + 1 < STEPS else half)
+    return psi
+
+
+def lumps(n, seed):
+    from paper_1909_08354_amd import inputs
+    L = tuple(float(v) for v in n)
+    rng = np.random.default_rng(seed)
+    cs, ws, vs = inputs.random_lumps(rng, n, L, 3, (min(n) / 8, min(n) / 5))
+    return inputs.lumps(n, L, cs, ws, vs), L
+
+
+def error(grid, psi, ref):
+    grid.set_psi(psi)
+    grid.step(STEPS)
+    out = grid.get_psi(np.complex128)
+    return float(np.sqrt((np.abs(out - ref) ** 2).sum() / (np.abs(ref) ** 2).sum()))
+
+
+def make_grid(n, L, storage, g):
+    from paper_1909_08354_amd import gsn
+    grid = gsn.Grid(n, L, storage=storage)
+    grid.set_kernel(*KERN)
+    grid.set_coefficients(0.5, g, DZ)
+    return grid
+
+
+# Errors of the 16-point plan with every rotation inside a butterfly a product of
+# its own, for the same inputs: the sum over seeds 1 to 3 in quadrature.
+E16_C128 = {(128, 128): 7.8699e-15, (256, 256): 1.4449e-14, (512, 256): 2.1134e-14, (1024, 256): 3.0959e-14,
+            (64, 64, 64): 6.8009e-15}
+
+
+@pytest.mark.parametrize("n", list(E16_C128), ids=str)
+def test_c128_error_of_the_16_point_plan(n):
+    """A complex128 grid is as exact as with plain rotations.  The figures repeat
+    exactly on one build; 2% is left for another order of the same roundings, which
+    moved the errors of seven shapes by -1.0% to +1.3%."""
+    total = 0.0
+    for seed in (1, 2, 3):
+        psi, L = lumps(n, seed)
+        g = -0.5 if len(n) == 2 else 0.0
+        grid = make_grid(n, L, np.complex128, g)
+        grid.set_schedule(0)
+        total += error(grid, psi, evolve_ld(psi, L, g)) ** 2
+        grid.close()
+    say(n, total ** 0.5)
+    assert total ** 0.5 <= 1.02 * E16_C128[n]

@@ -13,10 +13,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
 def test_fp64_butterflies_no_further_off_than_rounded_products(tmp_path):
-    """Where nothing is rounded to complex64, fusing a twiddle's product into the
-    addition and the subtraction must not cost accuracy: over every plan and both
-    kinds of line the error against extended precision stays at or below that of
-    products rounded on their own.  Half a percent is left for the sample: a line
+    """Where nothing is rounded to complex64, no twiddle's product may be fused
+    into the addition and the subtraction at a cost in accuracy: over every plan and
+    both kinds of line the error against extended precision stays at or below that
+    of products rounded on their own.  Half a percent is left for the sample: a line
     set has 2^17 values, and the two errors share most of their roundings."""
     exe = tmp_path / "host_fft"
     subprocess.run([HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950",
