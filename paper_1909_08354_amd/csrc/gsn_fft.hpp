@@ -104,7 +104,7 @@ __host__ __device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d
 // 12 steps of a complex128 256^2 state on the 16-point plan are 14% further off
 // (1.65e-14 against 1.45e-14; shapes with lines up to 1024 points 2% to 14%).
 // Beside values that are rounded to complex64 at the next exchange it vanishes, so
-// only complex128 values in complex128 slots are FULL.
+// the transforms through complex64 slots, and s4's of complex64 values, are short.
 template <int R, int S, bool TW, bool FULL = false, class W>
 __host__ __device__ __forceinline__ void dft(dc *a, const W &w)
 {

@@ -82,7 +82,10 @@ template <int N, int E, int LINES> struct LmTile {
 // complex128 (double2, the FP64-storage grids).  The argument structs carry
 // complex64 pointers; an FP64-storage kernel reinterprets them as double2
 // arrays (the host sets them to double2 buffers), and its LDS slots are
-// double2 too, so no value is rounded below FP64 anywhere in the step.
+// double2 too, so no value is rounded below FP64 anywhere in the step.  The
+// tiles take the type LT of their LDS slots apart from the type ST of the values
+// in HBM: at 4 points per thread (s4) complex64 values go through complex128
+// slots, since a short radix exchanges, and would round, more often.
 __device__ __forceinline__ dc ld_c(const float2 &v) { return from_f2(v); }
 __device__ __forceinline__ dc ld_c(const double2 &v) { return from_d2(v); }
 template <class ST> __device__ __forceinline__ ST st_c(dc v);
@@ -171,8 +174,8 @@ __device__ __forceinline__ void store_real_pair(const dc (&v)[E], bool act, int 
 
 // BOHM: also transform s = sqrt(rho) of both rows the same way into half2 /
 // nyq2 (the Bohm potential of Eq. (15) needs lap(s)).
-template <int N, int E, int LINES, bool STORE_PSI, bool REAL_IN = false, bool BOHM = false, class ST>
-__device__ __forceinline__ void density_tile(const EmArgs &a, int tile, ST *lds, double *sh)
+template <int N, int E, int LINES, bool STORE_PSI, bool REAL_IN = false, bool BOHM = false, class ST = float2, class LT>
+__device__ __forceinline__ void density_tile(const EmArgs &a, int tile, LT *lds, double *sh)
 {
     static_assert(!(STORE_PSI && REAL_IN), "real-space input is not stored back");
     constexpr int TPL = N / E, NT = LINES * TPL;
@@ -276,8 +279,8 @@ __device__ __forceinline__ void load_phi_pair(const EmArgs &a, bool act, int t, 
 }
 
 // Potential readout: phi rows (without the uniform k = 0 part) as float.
-template <int N, int E, int LINES>
-__device__ __forceinline__ void potential_tile(const EmArgs &a, int tile, float2 *lds)
+template <int N, int E, int LINES, class LT>
+__device__ __forceinline__ void potential_tile(const EmArgs &a, int tile, LT *lds)
 {
     constexpr int TPL = N / E;
     const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
@@ -463,8 +466,8 @@ inline void fill_sincos_table(double2 *tab)
 //
 // REAL_IN: the psi rows already hold psi in real space (written by the density
 // pass with STORE_PSI), so the inverse x transform is skipped.
-template <int N, int E, int LINES, bool ENERGY, bool REAL_IN, class ST>
-__device__ __forceinline__ void phase_tile(const EmArgs &a, int tile, ST *lds, double *sh)
+template <int N, int E, int LINES, bool ENERGY, bool REAL_IN, class ST = float2, class LT>
+__device__ __forceinline__ void phase_tile(const EmArgs &a, int tile, LT *lds, double *sh)
 {
     constexpr int TPL = N / E, NT = LINES * TPL;
     using RT = typename RealOf<ST>::T;
@@ -577,8 +580,8 @@ __device__ __forceinline__ double pressure_energy_density(const EmArgs &a, doubl
 // local_potential in place of g rho.  ENERGY: per tile the sums of rho phi,
 // rho^2, c_p G(rho) + V rho (pressure and static potential) and s lap(s)
 // (Bohm).
-template <int N, int E, int LINES, bool ENERGY, bool REAL_IN>
-__device__ __forceinline__ void phase_local_tile(const EmArgs &a, int tile, float2 *lds, double *sh)
+template <int N, int E, int LINES, bool ENERGY, bool REAL_IN, class LT>
+__device__ __forceinline__ void phase_local_tile(const EmArgs &a, int tile, LT *lds, double *sh)
 {
     constexpr int TPL = N / E, NT = LINES * TPL;
     const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
@@ -681,8 +684,8 @@ __device__ __forceinline__ void phase_local_tile(const EmArgs &a, int tile, floa
 // rows' half spectra (already carried through the other axes with -|k|^2);
 // then the real transform of s replaces those half spectra in place (each
 // tile reads its own two rows before writing them).
-template <int N, int E, int LINES, bool REAL_IN, bool LAP>
-__device__ __forceinline__ void source_tile(const EmArgs &a, int tile, float2 *lds)
+template <int N, int E, int LINES, bool REAL_IN, bool LAP, class LT>
+__device__ __forceinline__ void source_tile(const EmArgs &a, int tile, LT *lds)
 {
     constexpr int TPL = N / E;
     const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
@@ -779,8 +782,8 @@ struct LmArgs {
 // FP64 sum of the density pass's mass partials, folded into the state (below).
 template <int NT> __device__ __forceinline__ void reduce_mass(const LmArgs &a, double *sh);
 
-template <int N, int E, int LINES, int MODE, class ST>
-__device__ __forceinline__ void lm_tile(const LmArgs &a, int tile_in, ST *lds, double *sh)
+template <int N, int E, int LINES, int MODE, class ST = float2, class LT>
+__device__ __forceinline__ void lm_tile(const LmArgs &a, int tile_in, LT *lds, double *sh)
 {
     constexpr int TPL = N / E, NT = LINES * TPL;
     const int tid = threadIdx.x, l = tid % LINES, t = tid / LINES;
@@ -1951,52 +1954,52 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_em_fft(EmArgs a)
     __shared__ ST lds[EmTile<N, E, LINES>::LDS];
     em_fft_tile<N, E, LINES, S>(a, blockIdx.x, lds);
 }
-template <int N, int E, int LINES, bool STORE_PSI, bool BOHM = false, class ST = float2>
+template <int N, int E, int LINES, bool STORE_PSI, bool BOHM = false, class ST = float2, class LT = ST>
 __global__ __launch_bounds__(LINES *(N / E)) void k_density(EmArgs a)
 {
-    __shared__ ST lds[EmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double sh[EmTile<N, E, LINES>::NT / 64 + 1];
-    density_tile<N, E, LINES, STORE_PSI, false, BOHM>(a, blockIdx.x, lds, sh);
+    density_tile<N, E, LINES, STORE_PSI, false, BOHM, ST>(a, blockIdx.x, lds, sh);
 }
-template <int N, int E, int LINES, bool REAL_IN, bool LAP>
+template <int N, int E, int LINES, bool REAL_IN, bool LAP, class LT = float2>
 __global__ __launch_bounds__(LINES *(N / E)) void k_source(EmArgs a)
 {
-    __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     source_tile<N, E, LINES, REAL_IN, LAP>(a, blockIdx.x, lds);
 }
-template <int N, int E, int LINES, bool ENERGY, bool REAL_IN>
+template <int N, int E, int LINES, bool ENERGY, bool REAL_IN, class LT = float2>
 __global__ __launch_bounds__(LINES *(N / E)) void k_phase_local(EmArgs a)
 {
-    __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double sh[EmTile<N, E, LINES>::NT / 64 + 1];
     phase_local_tile<N, E, LINES, ENERGY, REAL_IN>(a, blockIdx.x, lds, sh);
 }
-template <int N, int E, int LINES>
+template <int N, int E, int LINES, class LT = float2>
 __global__ __launch_bounds__(LINES *(N / E)) void k_density_real(EmArgs a)
 {
-    __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double sh[EmTile<N, E, LINES>::NT / 64 + 1];
-    density_tile<N, E, LINES, false, true>(a, blockIdx.x, lds, sh);
+    density_tile<N, E, LINES, false, true, false, float2>(a, blockIdx.x, lds, sh);
 }
-template <int N, int E, int LINES, bool ENERGY, bool REAL_IN, class ST = float2>
+template <int N, int E, int LINES, bool ENERGY, bool REAL_IN, class ST = float2, class LT = ST>
 __global__ __launch_bounds__(LINES *(N / E)) void k_phase(EmArgs a)
 {
-    __shared__ ST lds[EmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double sh[EmTile<N, E, LINES>::NT / 64 + 1];
-    phase_tile<N, E, LINES, ENERGY, REAL_IN>(a, blockIdx.x, lds, sh);
+    phase_tile<N, E, LINES, ENERGY, REAL_IN, ST>(a, blockIdx.x, lds, sh);
 }
-template <int N, int E, int LINES>
+template <int N, int E, int LINES, class LT = float2>
 __global__ __launch_bounds__(LINES *(N / E)) void k_potential(EmArgs a)
 {
-    __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     potential_tile<N, E, LINES>(a, blockIdx.x, lds);
 }
-template <int N, int E, int LINES, int MODE, class ST = float2>
+template <int N, int E, int LINES, int MODE, class ST = float2, class LT = ST>
 __global__ __launch_bounds__(LINES *(N / E)) void k_lm(LmArgs a)
 {
-    __shared__ ST lds[LmTile<N, E, LINES>::LDS];
+    __shared__ LT lds[LmTile<N, E, LINES>::LDS];
     __shared__ double sh[LmTile<N, E, LINES>::NT / 64 + 1];
-    lm_tile<N, E, LINES, MODE>(a, blockIdx.x, lds, sh);
+    lm_tile<N, E, LINES, MODE, ST>(a, blockIdx.x, lds, sh);
 }
 
 // Waves per SIMD the persistent passes are held to.  x passes at 8 points per

@@ -7,27 +7,31 @@
 // unit of its own, so the library's objects build in parallel.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "gsn_host.hpp"
 
 template <int N, int V> static LKernels make_local_kernels()
 {
     using C = Cfg<N, V>;
     constexpr int E = C::E, LL = C::LM_LINES, EL = C::EM_LINES;
+    using LT = std::conditional_t<C::LAT, double2, float2>;   // LDS slots
     LKernels k;
-    k.density = k_density<N, E, EL, false, true>;
-    k.density_store = k_density<N, E, EL, true, true>;
-    k.phase = k_phase_local<N, E, EL, false, false>;
-    k.phase_real = k_phase_local<N, E, EL, false, true>;
-    k.phase_energy = k_phase_local<N, E, EL, true, false>;
-    k.lm_lap = k_lm<N, E, LL, LM_LAP>;
-    k.source[0][0] = k_source<N, E, EL, false, false>;
-    k.source[0][1] = k_source<N, E, EL, false, true>;
-    k.source[1][0] = k_source<N, E, EL, true, false>;
-    k.source[1][1] = k_source<N, E, EL, true, true>;
+    k.density = k_density<N, E, EL, false, true, float2, LT>;
+    k.density_store = k_density<N, E, EL, true, true, float2, LT>;
     if constexpr (C::LAT) {
         k.phase = k_sm_phase<N, false, float2, true>;
         k.phase_real = k_sm_phase<N, true, float2, true>;
+    } else {
+        k.phase = k_phase_local<N, E, EL, false, false>;
+        k.phase_real = k_phase_local<N, E, EL, false, true>;
     }
+    k.phase_energy = k_phase_local<N, E, EL, true, false, LT>;
+    k.lm_lap = k_lm<N, E, LL, LM_LAP, float2, LT>;
+    k.source[0][0] = k_source<N, E, EL, false, false, LT>;
+    k.source[0][1] = k_source<N, E, EL, false, true, LT>;
+    k.source[1][0] = k_source<N, E, EL, true, false, LT>;
+    k.source[1][1] = k_source<N, E, EL, true, true, LT>;
     k.density_p[0] = k.density_p[1] = nullptr;
     for (int i = 0; i < 8; ++i) {
         k.phase_p[i >> 2][(i >> 1) & 1][i & 1] = nullptr;

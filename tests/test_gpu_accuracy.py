@@ -87,3 +87,93 @@ def test_c128_error_of_the_16_point_plan(n):
         grid.close()
     say(n, total ** 0.5)
     assert total ** 0.5 <= 1.02 * E16_C128[n]
+
+
+# ---- read-outs and extra passes of the latency form against the 16-point plan
+def wavenumbers2(n, L):
+    k2 = np.zeros(n)
+    for ax in range(len(n)):
+        k = 2 * np.pi * np.fft.fftfreq(n[ax], d=L[ax] / n[ax])
+        k2 = k2 + (k * k).reshape([-1 if d == ax else 1 for d in range(len(n))])
+    return k2
+
+
+SMALL = [(64, 2048), (64, 128), (32, 32, 32), (64, 64, 64), (32, 256, 64)]
+
+
+def quadrature(errs):
+    return float(np.sqrt(np.sum(np.square(errs))))
+
+
+@pytest.mark.parametrize("n", SMALL, ids=str)
+def test_potential_of_an_untuned_small_grid(n):
+    """phi of a small grid's first schedule is no further off 64 bits than the
+    16-point plan's (2% for the sample of roundings)."""
+    errs = {}
+    for seed in (1, 2, 3):
+        psi, L = lumps(n, seed)
+        psi = psi.astype(np.complex64)
+        k2 = wavenumbers2(n, L)
+        K = np.where(k2 > 0, KERN[0] / np.where(k2 > 0, k2, 1) + KERN[1] / (k2 + KERN[2] ** 2), 0.0)
+        p = psi.astype(np.complex128)
+        ref = np.fft.ifftn(K * np.fft.fftn(p.real ** 2 + p.imag ** 2)).real
+        grid = make_grid(n, L, np.complex64, 0.0)
+        grid.set_psi(psi)
+        for name in ("first", "e16"):
+            if name == "e16":
+                grid.set_schedule(0)
+            phi = grid.potential().cpu().numpy().astype(np.float64)
+            errs.setdefault(name, []).append(np.linalg.norm(phi - ref) / np.linalg.norm(ref))
+        grid.close()
+    first, e16 = quadrature(errs["first"]), quadrature(errs["e16"])
+    say(n, first, e16, first / e16)
+    assert first <= 1.02 * e16
+
+
+@pytest.mark.parametrize("fields", [False, True], ids=["bohm", "source"])
+@pytest.mark.parametrize("n", SMALL, ids=str)
+def test_laplacians_of_an_untuned_small_grid(n, fields):
+    """One large step whose phase is the Laplacian term alone (the Bohm potential,
+    or a potential of lap(rho)): no further off 64 bits than the 16-point plan's."""
+    import torch
+    errs = {}
+    for seed in (1, 2, 3):
+        L = tuple(float(v) for v in n)
+        rng = np.random.default_rng(seed)
+        rho = np.ones(n)
+        for ax in range(len(n)):
+            x = np.arange(n[ax]) * (2 * np.pi / n[ax])
+            f = 1 + 0.3 * np.cos(3 * x + rng.uniform(0, 6)) + 0.1 * np.cos(int(n[ax] / 5) * x + rng.uniform(0, 6))
+            rho = rho * f.reshape([-1 if d == ax else 1 for d in range(len(n))])
+        psi = np.sqrt(rho).astype(np.complex64)
+        p = psi.astype(np.complex128)
+        rho = p.real ** 2 + p.imag ** 2
+        k2 = wavenumbers2(n, L)
+        grid = make_grid(n, L, np.complex64, 0.0)
+        if fields:
+            cN = 1.0
+            grid.set_kernel(cN, 0.0, 0.0, 0.0)
+            grid.set_source_fields(torch.zeros(n, device="cuda"), torch.ones(n, device="cuda"), None)
+            # K = cN / k^2 takes lap(rho) back to -cN (rho - mean)
+            U = -cN * (rho - rho.mean())
+            dz = 1.0
+        else:
+            grid.set_kernel(0.0, 0.0, 0.0, 0.0)
+            cb = -1.0
+            grid.set_local_terms(0.0, 1.0, cb, 1e-10)
+            s = np.sqrt(rho)
+            U = cb * np.fft.ifftn(-k2 * np.fft.fftn(s)).real / (2 * s)
+            dz = 1.0
+        grid.set_coefficients(0.0, 0.0, dz)   # no kinetic term: the phase alone
+        ref = p * np.exp(1j * U * dz)
+        for name in ("first", "e16"):
+            if name == "e16":
+                grid.set_schedule(0)
+            grid.set_psi(psi)
+            grid.step(1)
+            out = grid.get_psi(np.complex128)
+            errs.setdefault(name, []).append(np.linalg.norm(out - ref) / np.linalg.norm(ref))
+        grid.close()
+    first, e16 = quadrature(errs["first"]), quadrature(errs["e16"])
+    say(n, fields, first, e16, first / e16)
+    assert first <= 1.02 * e16
