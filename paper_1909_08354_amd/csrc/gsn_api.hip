@@ -892,28 +892,25 @@ static void fill_static_tables(gsn_grid g)
 // from 32^2 to 2048^2 and 32^3 to 512^3, plain, with local terms and with source
 // fields, against e16 in every pass:
 // - up to 2^19 points launches and their latencies bound a pass, not its
-//   throughput: s4 (64x128 35 -> 17 us, 512^2 59 -> 29, 1024x512 63 -> 45,
-//   32x256x64 60 -> 48; at 2^20 points p8 passes it, 1024^2 70 and 62 us;
-//   128x128x64 70 and 60).  The entry transform has one exchange less to
-//   wait for in s8 (64x2048 6.3 -> 6.0 us, 1024x512 5.3 -> 5.0, short lines
-//   equal); the exit stays with the density pass, whose inverse transform takes
-//   its place in a corrected step;
-// - above, p8 (512^3 5351 -> 3480 us, 512x256x256 942 -> 791, 2048^2 193 -> 133);
-//   on 256-point lines the kinetic passes have no load to hide behind a wider
-//   tile and take p16 (256^3 358 -> 336 us), and 2048-point lines in a grid of
-//   2^21 points or less have too few tiles for p8 (2048x1024 97 -> 90 us);
+//   throughput: s4 (64x128 35 -> 17 us, 512^2 64 -> 28, 1024x512 69 -> 45,
+//   32x256x64 64 -> 49; at 2^20 points 1024^2 takes 70 us with it and 69 with
+//   p16).  The entry transform has one exchange less to wait for in s8 (64x2048
+//   6.3 -> 6.0 us, 1024x512 5.3 -> 5.0, short lines equal); the exit stays with the
+//   density pass, whose inverse transform takes its place in a corrected step;
+// - above, p16: the plan of e16, so the same error (512^3 6735 -> 4202 us, 256^3
+//   383 -> 332, 2048^2 242 -> 152; 128^3, the shape that gains least, 86 -> 88).
+//   p8 is up to a quarter faster (512^3 3460 us, 2048^2 131, 128x128x64 59 against
+//   71), but its plan exchanges, and rounds to complex64, more often on lines of 16,
+//   128, 256, 1024 and 2048 points: psi is 3% to 37% further off 64 bits, and 5%
+//   where only one axis has 512 points.  Tuning may choose it, a first schedule not;
 // - complex128 grids above 2^19 points keep e16: their persistent passes are the
 //   one-tile passes (256^3 567 us, e8 613).
 constexpr long long kLatencyPoints = 1LL << 19;
 static int default_variant(gsn_grid g, int pass)
 {
-    enum { E16 = 0, P16 = 2, P8 = 3, S8 = 4 };
+    enum { E16 = 0, P16 = 2, S8 = 4 };
     if (g->P <= kLatencyPoints) return pass == P_ENTRY ? S8 : kSmallVariant;
-    if (g->storage == GSN_C128) return E16;
-    const int slow = g->ndim == 3 ? g->Nz : g->Ny;
-    if ((pass == P_KINETIC || pass == P_KERNEL) && slow == 2048 && g->P <= 1LL << 21) return P16;
-    const int line = pass == P_KINETIC ? slow : pass == P_KIN_Y ? g->Ny : 0;
-    return line == 256 ? P16 : P8;
+    return g->storage == GSN_C128 ? E16 : P16;
 }
 
 // ------------------------------------------------------------------ lifecycle

@@ -40,3 +40,19 @@ def test_default_schedule_agrees_with_e16(n, storage):
     d = np.linalg.norm(out[0] - out[1]) / np.linalg.norm(out[1])
     k = 3 * 9 * steps
     assert d <= (2 * np.sqrt(k) * 2.0 ** -24 if storage == np.complex64 else 64 * k * 2.0 ** -53)
+
+
+@pytest.mark.parametrize("n,storage,entry,rest", [
+    ((32, 32), np.complex64, "s8", "s4"), ((1024, 512), np.complex64, "s8", "s4"),
+    ((128, 64, 64), np.complex64, "s8", "s4"), ((1024, 1024), np.complex64, "p16", "p16"),
+    ((128, 128, 64), np.complex64, "p16", "p16"), ((8, 512, 256), np.complex64, "p16", "p16"),
+    ((512, 1024), np.complex128, "s8", "s4"), ((1024, 1024), np.complex128, "e16", "e16"),
+    ((64, 128, 128), np.complex128, "e16", "e16")])
+def test_first_schedule_by_size_and_storage(n, storage, entry, rest):
+    """The rule itself, on both sides of 2^19 points."""
+    g = gsn.Grid(n, [float(m) for m in n], storage=storage)
+    sched = g.schedule()
+    assert sched.pop("x_entry_fft") == entry
+    assert set(sched.values()) == {rest}
+    assert g.nonlinear_mode() == 0
+    g.close()
