@@ -1948,6 +1948,13 @@ __device__ __forceinline__ void densityp_body(const Src &src, LT *lds, double2 *
 // One grid: block b is tile b.  Grouped: several instances of one shape in
 // one launch; block b is tile (b mod tpi) of instance (b / tpi), whose
 // arguments are read from a device array.
+// Waves per SIMD that the density passes with the Bohm term are held to: two at 16
+// points per thread, up to 256-point rows (beyond, they spill).  Left alone they
+// take a few registers more than half the file and run at one: 256^3 79 us instead
+// of 100 (e16), 73.5 instead of 78 (p16; its storing form, 89 us, gains nothing),
+// 2048x64x64 35 instead of 41.
+template <int N, int E, bool BOHM = true> constexpr int bohm_waves() { return BOHM && E == 16 && N <= 256 ? 2 : 1; }
+
 template <int N, int E, int LINES, int S, class ST = float2>
 __global__ __launch_bounds__(LINES *(N / E)) void k_em_fft(EmArgs a)
 {
@@ -1955,7 +1962,7 @@ __global__ __launch_bounds__(LINES *(N / E)) void k_em_fft(EmArgs a)
     em_fft_tile<N, E, LINES, S>(a, blockIdx.x, lds);
 }
 template <int N, int E, int LINES, bool STORE_PSI, bool BOHM = false, class ST = float2, class LT = ST>
-__global__ __launch_bounds__(LINES *(N / E)) void k_density(EmArgs a)
+__global__ __launch_bounds__(LINES *(N / E), (bohm_waves<N, E, BOHM>())) void k_density(EmArgs a)
 {
     __shared__ LT lds[EmTile<N, E, LINES>::LDS];
     __shared__ double sh[EmTile<N, E, LINES>::NT / 64 + 1];
@@ -2030,7 +2037,7 @@ __global__ __launch_bounds__(LINES *(N / E), (em_waves<N, E>())) void k_phasep(E
 }
 // Pipelined forms of the Eq. (15) density (also sqrt(rho)) and phase passes.
 template <int N, int E, int LINES, bool STORE_PSI>
-__global__ __launch_bounds__(LINES *(N / E)) void k_densityp_bohm(EmArgs a)
+__global__ __launch_bounds__(LINES *(N / E), (bohm_waves<N, E, !STORE_PSI>())) void k_densityp_bohm(EmArgs a)
 {
     __shared__ float2 lds[EmTile<N, E, LINES>::LDS];
     __shared__ double2 twl[N];
