@@ -1602,9 +1602,17 @@ extern "C" gsn_status gsn_set_schedule(gsn_grid g, const int *variants, int npas
     return GSN_OK;
 }
 
+// Launches that may follow each other in place on the data of one fill.
+constexpr int kTimedLaunches = 8;
+
 // The launch of pass p in the current step schedule, redirected from psi to the
 // scratch buffer and with the end-of-step reduction switched off, so timing it
-// leaves the solver state untouched.
+// leaves the solver state untouched.  What it runs is what the step runs; only the
+// factors of values are chosen so that kTimedLaunches in place keep data in range:
+// the entry and exit transforms are unitary, the kernel and the Laplacians are 1 / N
+// in the middle of the spectrum (on a step's own factor, 1 / (2 P), complex64
+// underflows within a few launches).  The plain y transforms keep their scale of 1,
+// which spares them two multiplications a point; they grow the norm by sqrt(Ny).
 static bool timing_launch(gsn_grid g, int p, Launch *out)
 {
     const std::vector<Launch> *lists[] = {&g->entry, &g->kin_full, &g->nonlin, &g->exit_};
@@ -1618,36 +1626,68 @@ static bool timing_launch(gsn_grid g, int p, Launch *out)
                     if (out->la.s0.ptr == g->psi) out->la.s0.ptr = g->scratch;
                     out->la.reduce = 0;
                 }
-                // the plain transforms are unnormalised in the step (their
-                // scale sits in another pass); repeated in place they would
-                // grow the data by up to N per launch and reach Inf.  Timed
-                // with the unitary scale 1/sqrt(N) they keep its norm, and the
-                // scale multiply costs the same
                 if (p == P_ENTRY || p == P_EXIT) out->ea.scale = 1.0 / std::sqrt((double)g->Nx);
-                const bool ftrans = p == P_Y_FWD_RHO ||
-                                    p == P_Y_INV_PHI || p == P_Y_FWD_SQRT || p == P_Y_INV_LAP ||
-                                    p == P_Y_FWD_SRC || p == P_Y_INV_SRC;
-                if (ftrans) out->la.scale = 1.0 / std::sqrt((double)g->Ny);   // the y axis (3-D only)
+                if (p == P_KERNEL || p == P_LAPLACIAN || p == P_LAP_RHO) {
+                    double lo = 1e300, hi = 0.0;
+                    for (int d = 0; d < g->ndim; ++d) {
+                        const double k1 = wavenumber(1, g->n[d], g->L[d]), kn = wavenumber(g->n[d] / 2, g->n[d], g->L[d]);
+                        lo = std::min(lo, k1 * k1);
+                        hi += kn * kn;
+                    }
+                    const double k2 = std::sqrt(lo * hi);
+                    const double N = g->ndim == 3 ? g->Nz : g->Ny;
+                    LmArgs &a = out->la;
+                    const double mid = p == P_KERNEL ? std::fabs(a.cN / k2 + a.cY / (k2 + a.mY2) + a.c0) : k2 * a.scale;
+                    const double f = 1.0 / (N * mid);
+                    if (std::isfinite(f) && f > 0.0) {   // otherwise no kernel, or a pole
+                        a.cN *= f;
+                        a.cY *= f;
+                        a.c0 *= f;
+                        a.scale *= f;
+                    }
+                }
                 return true;
             }
     return false;
 }
 
-static gsn_status time_launch(gsn_grid g, const Launch &L, int iters, double *ms)
+// The data pass p is timed on: a copy of psi in scratch and, behind the density
+// pass, the half spectra that pass makes of it.
+static gsn_status timing_fill(gsn_grid g, int p)
 {
+    if (g->have_psi)
+        HIP_TRY(hipMemcpyAsync(g->scratch, g->psi, g->esz * g->P, hipMemcpyDeviceToDevice, g->stream));
+    Launch L;
+    if (p > P_DENSITY && p != P_EXIT && timing_launch(g, P_DENSITY, &L)) HIP_TRY(launch(L, g->stream));
+    return GSN_OK;
+}
+
+// Average of iters launches of pass p on fresh data: filled again, and two launches
+// left out, every kTimedLaunches.
+static gsn_status time_launch(gsn_grid g, int p, const Launch &L, int iters, double *ms)
+{
+    constexpr int kUntimed = 2;
     hipEvent_t a, b;
     HIP_TRY(hipEventCreate(&a));
     HIP_TRY(hipEventCreate(&b));
-    for (int i = 0; i < 2; ++i) HIP_TRY(launch(L, g->stream));
-    HIP_TRY(hipEventRecord(a, g->stream));
-    for (int i = 0; i < iters; ++i) HIP_TRY(launch(L, g->stream));
-    HIP_TRY(hipEventRecord(b, g->stream));
-    HIP_TRY(hipEventSynchronize(b));
-    float t = 0.f;
-    HIP_TRY(hipEventElapsedTime(&t, a, b));
+    double total = 0.0;
+    for (int done = 0; done < iters;) {
+        const int n = std::min(iters - done, kTimedLaunches - kUntimed);
+        const gsn_status s = timing_fill(g, p);
+        if (s) return s;
+        for (int i = 0; i < kUntimed; ++i) HIP_TRY(launch(L, g->stream));
+        HIP_TRY(hipEventRecord(a, g->stream));
+        for (int i = 0; i < n; ++i) HIP_TRY(launch(L, g->stream));
+        HIP_TRY(hipEventRecord(b, g->stream));
+        HIP_TRY(hipEventSynchronize(b));
+        float t = 0.f;
+        HIP_TRY(hipEventElapsedTime(&t, a, b));
+        total += t;
+        done += n;
+    }
     HIP_TRY(hipEventDestroy(a));
     HIP_TRY(hipEventDestroy(b));
-    *ms = (double)t / iters;
+    *ms = total / iters;
     return GSN_OK;
 }
 
@@ -1754,11 +1794,8 @@ extern "C" gsn_status gsn_autotune(gsn_grid g, int iters)
             Launch L;
             if (!timing_launch(g, p, &L)) break;
             present[p] = true;
-            // every variant starts from the same data
-            if (g->have_psi)
-                HIP_TRY(hipMemcpyAsync(g->scratch, g->psi, g->esz * g->P, hipMemcpyDeviceToDevice, g->stream));
             double ms = 0.0;
-            gsn_status s = time_launch(g, L, iters, &ms);
+            gsn_status s = time_launch(g, p, L, iters, &ms);
             if (s) return s;
             if (ms < best_ms) { best_ms = ms; best = v; }
         }
