@@ -79,7 +79,9 @@ gsn_status gsn_workspace_bytes(int ndim, const int32_t n[], size_t *bytes);
 /* Create a solver on the current HIP device.  d_workspace: device pointer,
    256-byte aligned, at least gsn_workspace_bytes() bytes, owned by the caller.
    L[]: box lengths > 0 (C order).  hip_stream: a hipStream_t or NULL.
-   Defaults after creation: a = 1/2, g = 0, dz = 0 (must be set), kernel = 0. */
+   Also takes 9 KiB of pinned host memory, in which mass, energy and state are
+   read out; gsn_destroy frees it.  Where that is refused they are copied from
+   the workspace instead.  Defaults after creation: a = 1/2, g = 0, dz = 0 (must be set), kernel = 0. */
 gsn_status gsn_create(gsn_grid *out, int ndim, const int32_t n[], const double L[],
                       void *d_workspace, size_t bytes, void *hip_stream);
 
@@ -237,10 +239,18 @@ double gsn_pass_bytes_per_point(gsn_grid grid, int i);
    pass for such grids (4 points per thread up to 256-point lines, FP64
    exchanges, both rows of a pair together).  A variant changes the Stockham radix plan, the
    tile shape and the LDS footprint, never the result beyond rounding.
-   A new grid starts with variants chosen by its size and storage.
-   gsn_autotune times every variant of every pass of this grid (iters launches
-   each, on a scratch copy of psi: the state is not modified) and keeps the
-   fastest.  If the environment variable GSN_AUTOTUNE_CACHE names a file,
+   The 8- and 4-point plans exchange more often than the 16-point plan on most
+   lengths.  A complex64 grid rounds to complex64 at each exchange (s4 does not),
+   so its states are up to a third further off 64 bits in e8, p8 and s8 than in
+   e16 and p16.  A new grid starts with variants that are no further off than
+   e16: by its size and storage s4 (s8 for the entry transform), p16 or e16.
+   gsn_autotune chooses by time alone, on scratch copies (the state is not
+   modified; iters launches of each): every variant of every pass -- s4 up to
+   2^21 points --, then the nonlinear mode by whole steps, for mode 1 with every
+   variant of the density pass and then, beside the best of those, of the phase
+   pass; up to 2^21 points also s4 in all passes but entry and exit, by whole
+   steps, unless a choice came from the file.
+   If the environment variable GSN_AUTOTUNE_CACHE names a file,
    choices are read from it (key: GPU architecture, grid shape, pass) and new
    ones appended.  Synchronising. */
 int gsn_variant_count(void);

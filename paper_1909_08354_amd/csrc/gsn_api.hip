@@ -1994,7 +1994,12 @@ extern "C" gsn_status gsn_step_corrected(gsn_grid g, gsn_corrector c, int64_t nc
             if ((s = run_lists(g, g->coarse, 1))) return s;
             if ((s = run_potential(g, phi))) return s;
         }
-        if ((s = corrector_correct(c, coarse, phi, g->psi, &g->st->theta, g->stream))) return s;
+        if ((s = corrector_correct(c, coarse, phi, g->psi, &g->st->theta, g->stream))) {
+            // without the network's result the coarse step's state is the state
+            if (coarse != g->psi)
+                (void)hipMemcpyAsync(g->psi, coarse, bytes, hipMemcpyDeviceToDevice, g->stream);
+            return s;
+        }
         if (audit) {
             // the fine solver from the same state is the reference for the corrected step
             HIP_TRY(hipMemcpyAsync(corrected, g->psi, bytes, hipMemcpyDeviceToDevice, g->stream));
