@@ -1308,8 +1308,10 @@ extern "C" gsn_status gsn_step(gsn_grid g, int64_t nsteps)
 static gsn_status read_obs(gsn_grid g, const ObsArgs &cols, HostObs *out)
 {
     HostObs *dst = g->obs_host ? g->obs_host : g->obs_dev;
-    hipLaunchKernelGGL(k_obs, dim3(cols.ncol + 1), dim3(256), 0, g->stream, cols, g->st, dst);
-    HIP_TRY(hipGetLastError());
+    // the launch's own status: the thread's last error may be another library's
+    ObsArgs c = cols;
+    void *args[] = {&c, &g->st, &dst};
+    HIP_TRY(hipLaunchKernel((const void *)k_obs, dim3(cols.ncol + 1), dim3(256), args, 0, g->stream));
     if (!g->obs_host) HIP_TRY(hipMemcpyAsync(out, dst, sizeof(HostObs), hipMemcpyDeviceToHost, g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));
     if (g->obs_host) *out = *g->obs_host;

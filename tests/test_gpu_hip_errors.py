@@ -72,3 +72,15 @@ def test_failed_network_leaves_the_coarse_state(foreign):
     d = np.linalg.norm(out[1] - out[0]) / np.linalg.norm(out[0])
     # the same passes but the last inverse transform: storage roundings only
     assert d < 2 * np.sqrt(3 * 9) * 2.0 ** -24
+
+
+def test_state_read_outs_report_their_own_errors(foreign):
+    """sync and phase succeed whatever another call of the thread has left."""
+    g = make_grid((64, 128))
+    g.step(3)
+    want = g.phase()
+    foreign.leave()
+    g.sync()
+    assert g.phase() == want
+    foreign.take()
+    g.close()
