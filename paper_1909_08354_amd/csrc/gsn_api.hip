@@ -35,33 +35,35 @@ template <int N, int V> static NKernels make_kernels()
     k.TPL = C::TPL;
     k.lm_lines = LL;
     k.em_lines = EL;
-    k.em_fwd = k_em_fft<N, E, EL, -1>;
-    k.em_inv = k_em_fft<N, E, EL, 1>;
-    k.density = k_density<N, E, EL, false>;
-    k.density_store = k_density<N, E, EL, true>;
-    k.density_real = k_density_real<N, E, EL>;
-    k.phase = k_phase<N, E, EL, false, false>;
-    k.phase_real = k_phase<N, E, EL, false, true>;
-    k.phase_energy = k_phase<N, E, EL, true, false>;
-    k.potential = k_potential<N, E, EL>;
-    k.lm_fwd = k_lm<N, E, LL, LM_FWD>;
-    k.lm_inv = k_lm<N, E, LL, LM_INV>;
-    k.lm_kin = k_lm<N, E, LL, LM_KIN>;
-    k.lm_kern = k_lm<N, E, LL, LM_KERN>;
-    k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY>;
     for (int m = 0; m < 4; ++m) k.lmp[m] = k.lmp2[m] = nullptr;
     k.em_pipe = C::PIPE;
+    if constexpr (V == kSmallVariant) {
+        small_kernels<N, float2>(k);
+        return k;
+    } else {
+        k.em_fwd = k_em_fft<N, E, EL, -1>;
+        k.em_inv = k_em_fft<N, E, EL, 1>;
+        k.density = k_density<N, E, EL, false>;
+        k.density_store = k_density<N, E, EL, true>;
+        k.density_real = k_density_real<N, E, EL>;
+        k.phase = k_phase<N, E, EL, false, false>;
+        k.phase_real = k_phase<N, E, EL, false, true>;
+        k.phase_energy = k_phase<N, E, EL, true, false>;
+        k.potential = k_potential<N, E, EL>;
+        k.lm_fwd = k_lm<N, E, LL, LM_FWD>;
+        k.lm_inv = k_lm<N, E, LL, LM_INV>;
+        k.lm_kin = k_lm<N, E, LL, LM_KIN>;
+        k.lm_kern = k_lm<N, E, LL, LM_KERN>;
+        k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY>;
+    }
     if constexpr (C::PIPE) {
         k.density = k_densityp<N, E, EL, false>;
         k.density_store = k_densityp<N, E, EL, true>;
         k.phase = k_phasep<N, E, EL, false>;
         k.phase_real = k_phasep<N, E, EL, true>;
-        k.lmp[LM_FWD] = k_lmp<N, E, LL, LM_FWD, float2>;
-        k.lmp[LM_INV] = k_lmp<N, E, LL, LM_INV, float2>;
-        k.lmp[LM_KIN] = k_lmp<N, E, LL, LM_KIN, float2>;
-        k.lmp[LM_KERN] = k_lmp<N, E, LL, LM_KERN, float2>;
         using T = TwoButterfly<N>;
-        if constexpr (V == 3 && T::ON) {
+        constexpr bool TWO = V == 3 && T::ON;
+        if constexpr (TWO) {
             k.lmp2[LM_FWD] = k_lmp2<N, T::LINES, LM_FWD>;
             k.lmp2[LM_INV] = k_lmp2<N, T::LINES, LM_INV>;
             k.lmp2[LM_KIN] = k_lmp2<N, T::LINES, LM_KIN>;
@@ -70,8 +72,15 @@ template <int N, int V> static NKernels make_kernels()
             k.lmp2_threads = T::THREADS;
             k.lmp2_min_tiles = T::MIN_TILES;
         }
+        // where the two-butterfly form has the same tiles and takes any number of
+        // them, no pass is left for the one-butterfly form
+        if constexpr (!(TWO && T::LINES == LL && T::MIN_TILES == 0)) {
+            k.lmp[LM_FWD] = k_lmp<N, E, LL, LM_FWD, float2>;
+            k.lmp[LM_INV] = k_lmp<N, E, LL, LM_INV, float2>;
+            k.lmp[LM_KIN] = k_lmp<N, E, LL, LM_KIN, float2>;
+            k.lmp[LM_KERN] = k_lmp<N, E, LL, LM_KERN, float2>;
+        }
     }
-    if constexpr (V == kSmallVariant) small_kernels<N, float2>(k);
     return k;
 }
 

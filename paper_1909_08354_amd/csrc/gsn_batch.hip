@@ -213,14 +213,15 @@ template <int N, int V> GKernels make_gkernels()
         k.density_store = (const void *)k_densityp_g<N, E, EL, true>;
         k.phase = (const void *)k_phasep_g<N, E, EL, false>;
         k.phase_real = (const void *)k_phasep_g<N, E, EL, true>;
-        k.lm_kin = (const void *)k_lmp_g<N, E, LL, LM_KIN>;
-        k.lm_kern = (const void *)k_lmp_g<N, E, LL, LM_KERN>;
         using T = TwoButterfly<N>;
         if constexpr (V == 3 && T::BATCH) {
             k.lm_kin = (const void *)k_lmp2_g<N, T::LINES, LM_KIN>;
             k.lm_kern = (const void *)k_lmp2_g<N, T::LINES, LM_KERN>;
             k.lm_lines = T::LINES;
             k.lm_nt = T::THREADS;
+        } else {
+            k.lm_kin = (const void *)k_lmp_g<N, E, LL, LM_KIN>;
+            k.lm_kern = (const void *)k_lmp_g<N, E, LL, LM_KERN>;
         }
     } else {
         k.density = (const void *)k_density_g<N, E, EL, false>;

@@ -20,23 +20,25 @@ template <int N, int V> static NKernels make_kernels_c128()
     k.TPL = C::TPL;
     k.lm_lines = LL;
     k.em_lines = EL;
-    k.em_fwd = k_em_fft<N, E, EL, -1, D>;
-    k.em_inv = k_em_fft<N, E, EL, 1, D>;
-    k.density = k_density<N, E, EL, false, false, D>;
-    k.density_store = k_density<N, E, EL, true, false, D>;
-    k.density_real = nullptr;   // no potential readout on these grids
-    k.phase = k_phase<N, E, EL, false, false, D>;
-    k.phase_real = k_phase<N, E, EL, false, true, D>;
-    k.phase_energy = k_phase<N, E, EL, true, false, D>;
-    k.potential = nullptr;
-    k.lm_fwd = k_lm<N, E, LL, LM_FWD, D>;
-    k.lm_inv = k_lm<N, E, LL, LM_INV, D>;
-    k.lm_kin = k_lm<N, E, LL, LM_KIN, D>;
-    k.lm_kern = k_lm<N, E, LL, LM_KERN, D>;
-    k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY, D>;
     for (int m = 0; m < 4; ++m) k.lmp[m] = k.lmp2[m] = nullptr;
     k.em_pipe = false;
-    if constexpr (V == kSmallVariant) small_kernels<N, D>(k);
+    k.density_real = k.potential = nullptr;   // no potential readout on these grids
+    if constexpr (V == kSmallVariant) {
+        small_kernels<N, D>(k);
+    } else {
+        k.em_fwd = k_em_fft<N, E, EL, -1, D>;
+        k.em_inv = k_em_fft<N, E, EL, 1, D>;
+        k.density = k_density<N, E, EL, false, false, D>;
+        k.density_store = k_density<N, E, EL, true, false, D>;
+        k.phase = k_phase<N, E, EL, false, false, D>;
+        k.phase_real = k_phase<N, E, EL, false, true, D>;
+        k.phase_energy = k_phase<N, E, EL, true, false, D>;
+        k.lm_fwd = k_lm<N, E, LL, LM_FWD, D>;
+        k.lm_inv = k_lm<N, E, LL, LM_INV, D>;
+        k.lm_kin = k_lm<N, E, LL, LM_KIN, D>;
+        k.lm_kern = k_lm<N, E, LL, LM_KERN, D>;
+        k.lm_kin_energy = k_lm<N, E, LL, LM_KIN_ENERGY, D>;
+    }
     return k;
 }
 
