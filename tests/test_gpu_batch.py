@@ -301,3 +301,41 @@ def test_masses_and_state_of_many_or_tiny_instances(count, n):
     b.step(1)
     with pytest.raises(gsn.GsnError):
         b.sync()
+
+
+TWO_BUTTERFLY = [(256, 64, 5), (512, 64, 5), (2048, 32, 3)]   # column length, row length, instances
+
+
+@pytest.mark.parametrize("ny,nx,count", TWO_BUTTERFLY, ids=str)
+@pytest.mark.parametrize("uniform", [True, False])
+def test_p8_columns_of_a_batch_equal_a_grids(ny, nx, count, uniform):
+    """The grouped two-butterfly column passes (p8 on 256-, 512- and 2048-point
+    columns; 2048 with its table in global memory) give the bits of the single
+    grid's.  Instances of other steps dz share no tables, so their group takes the
+    one-tile passes of the same plan instead: the same bits again."""
+    n = (ny, nx)
+    L = (float(ny), float(nx))
+    rng = np.random.default_rng(11)
+    sched = [3, 1, 3, 1, 1]
+    b = gsn.Batch([n] * count, [L] * count)
+    b.set_schedule(sched, 0)
+    inst = []
+    for i in range(count):
+        cs, ws, vs = inputs.random_lumps(rng, n, L, 2, (min(n) / 8, min(n) / 5))
+        psi = inputs.to_c64(inputs.lumps(n, L, cs, ws, vs))
+        kern = (1.0, 0.1 * i, 0.2 + 0.1 * i, 0.0)
+        dz = 1e-3 if uniform else 1e-3 * (1 + i)
+        b.set(i, kern, 0.5, -0.5, dz, psi)
+        inst.append((kern, dz, psi))
+    say("batch", n, "uniform", uniform)
+    b.step(4)
+    for i, (kern, dz, psi) in enumerate(inst):
+        g = gsn.Grid(n, L)
+        g.set_kernel(*kern)
+        g.set_coefficients(0.5, -0.5, dz)
+        g.set_schedule(grid_schedule(g, sched))
+        g.set_psi(psi)
+        g.step(4)
+        assert np.array_equal(b.get(i, np.complex64), g.get_psi(np.complex64)), i
+        assert b.phase(i) == g.phase()
+        g.close()

@@ -56,3 +56,34 @@ def test_non_finite_values_are_reported(bad):
     with pytest.raises(gsn.GsnError):
         g.step(1)
         g.sync()
+
+
+@pytest.mark.parametrize("n", [(32, 32, 2048), (64, 64, 512), (128, 64, 512)])
+def test_energies_from_long_columns_match_their_definition(n):
+    """Columns of 2048 and 4096 values (s4: a partial per wave), both sides of what a
+    block of 256 threads takes in one round of eight loads.  Kinetic as above; the
+    non-local energy is of fourth order in psi, so twice that bar."""
+    rng = np.random.default_rng(8)
+    x = [np.arange(m) * (2 * np.pi / m) for m in n]
+    amp = 1.0
+    for ax in range(3):
+        f = 1 + 0.4 * np.cos(x[ax] + rng.uniform(0, 6)) + 0.2 * np.cos(3 * x[ax] + rng.uniform(0, 6))
+        amp = amp * f.reshape([-1 if d == ax else 1 for d in range(3)])
+    psi = (amp * np.exp(0.5j * amp)).astype(np.complex64)
+    L = [float(m) for m in n]
+    g = gsn.Grid(n, L)
+    g.set_kernel(1.0, 0.3, 0.5, 0.0)
+    g.set_coefficients(0.5, 0.0, 1e-3)
+    g.set_schedule(gsn.variant_names().index("s4"))
+    g.set_psi(psi)
+    e = g.energy()
+    P = np.prod(n)
+    p = psi.astype(np.complex128)
+    k2 = sum(np.meshgrid(*[(2 * np.pi * np.fft.fftfreq(m)) ** 2 for m in n], indexing="ij"))
+    kin = 0.5 * np.sum(k2 * np.abs(np.fft.fftn(p)) ** 2) / P   # dV = 1
+    rho = np.abs(p) ** 2
+    K = np.where(k2 > 0, 1.0 / np.where(k2 > 0, k2, 1.0), 0.0) + 0.3 / (k2 + 0.25)
+    non = -0.5 * np.sum(rho * np.fft.ifftn(K * np.fft.fftn(rho)).real)
+    assert abs(e["kinetic"] - kin) <= 4 * 24 * 2.0 ** -24 * abs(kin)
+    assert abs(e["nonlocal"] - non) <= 8 * 24 * 2.0 ** -24 * abs(non)
+    g.close()

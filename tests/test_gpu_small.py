@@ -105,3 +105,23 @@ def test_local_terms_and_static_potential(n, mode):
     g.step(12)
     ref = orc.evolve_fields(psi, L, (0.5, 0.3, 0.2, 0.0), 0.5, -0.2, 1e-3, 12, (None, None, V), local=local)
     assert orc.rel_l2(g.get_psi(), ref) < BAR[np.complex64]
+
+
+@pytest.mark.parametrize("n", [(64, 64, 512), (128, 64, 512)])
+def test_mass_block_sums_several_rounds(n):
+    """2048 and 4096 partial sums in the block that sums them: one and two rounds of
+    its eight loads a thread.  After one step theta = K(0) dz <rho>; the kinetic half
+    step keeps the mass, and rho is quadratic in values stored as complex64 by at
+    most four passes before the density pass: 2 * 4 * 3 roundings of 2^-24."""
+    rng = np.random.default_rng(9)
+    psi = (rng.standard_normal(n) + 1j * rng.standard_normal(n)).astype(np.complex64)
+    grid = gsn.Grid(n, [float(v) for v in n])
+    grid.set_kernel(0.0, 0.0, 0.0, 0.7)
+    grid.set_coefficients(0.5, 0.0, DZ)
+    grid.set_schedule(gsn.variant_names().index("s4"))
+    grid.set_psi(psi)
+    grid.step(1)
+    theta, steps = grid.phase()
+    want = 0.7 * DZ * np.mean(np.abs(psi.astype(np.complex128)) ** 2)
+    assert steps == 1 and abs(theta - want) <= 24 * 2.0 ** -24 * want
+    grid.close()
