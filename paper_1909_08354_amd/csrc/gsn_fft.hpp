@@ -92,11 +92,13 @@ __host__ __device__ __forceinline__ void dft4_out(double c, dc s02, dc s13, dc d
 }
 
 // Length-R DFT in registers, natural order in and out; TW: point r is first
-// multiplied by w(r) (r >= 1).  The FFT passes are bound by FP64 issue (a
-// 256-point kinetic pass issues for 95% of its time), so the multiplications
-// go into the additions that follow them: a twiddled first-layer pair takes
-// 10 instructions instead of 12 (6 instead of 8 for point 0), and a constant
-// rotation is applied as c (1, tan) with c folded into the next layer's FMAs
+// multiplied by w(r) (r >= 1).  FP64 issue bounds the FFT passes more than memory
+// does (a 256-point kinetic pass of 256^3 issues 65 VALU instructions a point, 16.6
+// thousand per SIMD: 36 to 45 of its 54 us at the 2.2 to 2.7 ns that an FP64 one
+// takes), so the multiplications go into the additions that follow them: a
+// twiddled first-layer pair takes 10 instructions instead of 12 (6 instead of 8 for
+// point 0), and a constant rotation is applied as c (1, tan) with c folded into the
+// next layer's FMAs
 // (cos pi/8 or sqrt(1/2); the tangent never exceeds 1).
 // FULL: products with twiddles, and with cos and sin of pi/8, are rounded on their
 // own.  The short forms err by 1% to 3% more per transform (lines of 16 to 2048

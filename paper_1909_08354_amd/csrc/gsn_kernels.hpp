@@ -143,8 +143,8 @@ __device__ __forceinline__ void em_fft_tile(const EmArgs &a, int tile, ST *lds)
 // r0, r1 and the real bin N/2 to nyq.  The factor 2 is taken out by the
 // multiplier pass that follows, as are the transforms' 1/N (powers of two: the
 // same bits; the density, phase and plain strided passes are bound by FP64 issue
-// at 256^3 and lose 1 to 2 multiplications a point: x_density 48.1 -> 46.9 us,
-// x_phase 89.4 -> 87.0, and 512^3 y_fwd_rho 222 -> 216).
+// and lose 1 to 2 multiplications a point: 512^3 y_fwd_rho 222 -> 216 us, the x
+// passes of 256^3, at 47 and 81 us now, 2% to 3%).
 template <int N, int E, class LT, class ST>
 __device__ __forceinline__ void store_real_pair(const dc (&v)[E], bool act, int t, const EmLayout<N, E> &lay,
                                                 LT *lds, ST *half, ST *nyq, long long r0, long long r1)
